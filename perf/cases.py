@@ -1,0 +1,434 @@
+"""Performance cases of the Poisson MaZe library.
+
+Each case is one pass through a public entry point on synthetic molten NaCl
+(or the bcc start of the paper's own salt), from the smallest workload, 64
+ions on a 32^3 grid, to the largest, 32768 ions on a 256^3 grid:
+
+  md        one MD step of one system (md.MDRun.step)
+  step      one MaZe step with field, forces and energy (maze.Session.step)
+  solve     one direct Poisson solve from a zero guess (maze.Session.solve)
+  ensemble  one MD step of many replicas together (maze_md_step_batch)
+  serve     one MD step of each of several sessions as a burst of requests to
+            a continuous batch (maze.Batch)
+  rdf       pair-distance histograms of one frame (observables.PairHistogram)
+
+The options of a case: `cells` (conventional rock-salt cells per side, 8
+cells^3 ions), `N` (grid points per side), `order` (assignment), `mixed`
+(FP32 inner solves, else FP64), `tol` (relative residual), `form` (the CG:
+"sweep", one fused sweep per iteration and the library's default; "sstep",
+two iterations per pass pair; "mg", multigrid-preconditioned).
+"""
+import math
+
+import numpy as np
+import torch
+
+from paper_2505_20418_amd import inputs, maze, md, observables
+
+FORMS = {"sweep": 0, "sstep": maze.MAZE_FLAG_SSTEP, "mg": maze.MAZE_FLAG_MULTIGRID}
+
+
+def listed():
+    return [
+        # the smallest system of the test and benchmark workloads, FP64, as a
+        # plain md.MDRun(system, tol) runs it: launches and latency
+        dict(name="md_g32_fp64", kind="md", cells=2, N=32, order=2, mixed=False, tol=1e-9,
+             form="sweep", langevin=False),
+        # a caller with its own integrator: one MaZe step on a ragged grid,
+        # loose tolerance class of the serving mix
+        dict(name="step_g50_mixed", kind="step", cells=3, N=50, order=2, mixed=True, tol=1e-6,
+             form="sstep"),
+        # a mid-size session of the serving mix in the library's default form
+        dict(name="md_g64_mixed_sweep", kind="md", cells=4, N=64, order=2, mixed=True, tol=1e-6,
+             form="sweep", langevin=False),
+        # the baseline solver of the convergence study: a cold direct solve,
+        # grid not a multiple of the 8-point tiles
+        dict(name="solve_g100_fp64", kind="solve", cells=6, N=100, order=2, mixed=False, tol=1e-9,
+             form="sweep"),
+        # the paper's own salt: 250 ions, 20.64 A, h = 0.172 A, cubic
+        # B-splines, canonical equilibration (OVRVO)
+        dict(name="md_bcc250_g120_langevin", kind="md", cells=5, N=120, order=4, mixed=False,
+             tol=1e-8, form="sstep", langevin=True, bcc=True),
+        # 4096 ions, 128^3, FP64, tol 1e-9
+        dict(name="md_g128_fp64", kind="md", cells=8, N=128, order=2, mixed=False, tol=1e-9,
+             form="sstep", langevin=False),
+        # the headline workload: 32768 ions, 256^3, relative residual 1e-8,
+        # mixed precision and FP64
+        dict(name="md_g256_mixed", kind="md", cells=16, N=256, order=2, mixed=True, tol=1e-8,
+             form="sstep", langevin=False),
+        dict(name="md_g256_fp64", kind="md", cells=16, N=256, order=2, mixed=False, tol=1e-8,
+             form="sstep", langevin=False),
+        # the same system with the multigrid preconditioner
+        dict(name="md_g256_mixed_mg", kind="md", cells=16, N=256, order=2, mixed=True, tol=1e-8,
+             form="mg", langevin=False),
+        # replica sampling: 64 uneven replicas, 32^3 to 96^3
+        dict(name="ensemble64_mixed", kind="ensemble", count=64, mixed=True, tol=1e-8,
+             form="sstep", draw_seed=4),
+        # serving: a burst of 16 requests on sessions of 32^3 to 128^3, half
+        # mixed at 1e-6 and half FP64 at 1e-10
+        dict(name="serve16", kind="serve", count=16, form="sstep", draw_seed=5),
+        # structure analysis of one frame of the largest system
+        dict(name="rdf_32768", kind="rdf", cells=16, nbins=240, r_max=12.0),
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    kind = rng.choice(["md"] * 6 + ["step"] * 3 + ["solve"] * 2 + ["ensemble", "serve", "rdf"])
+    if kind == "rdf":
+        cells = _log_int(rng, 3, 16)
+        return dict(kind=kind, cells=cells, nbins=rng.randint(50, 400),
+                    r_max=round(min(12.0, 0.5 * cells * inputs.LATTICE_A) * rng.uniform(0.6, 1.0), 3))
+    if kind == "ensemble":
+        return dict(kind=kind, count=rng.randint(8, 48), mixed=rng.random() < 0.5,
+                    tol=rng.choice([1e-8, 1e-9]), form=rng.choice(["sstep", "sstep", "sweep"]),
+                    draw_seed=rng.randint(10, 1 << 20))
+    if kind == "serve":
+        return dict(kind=kind, count=rng.randint(6, 16), form=rng.choice(["sstep", "sstep", "sweep"]),
+                    draw_seed=rng.randint(10, 1 << 20))
+    form = rng.choice(["sstep"] * 4 + ["sweep"] * 3 + ["mg"])
+    if form == "mg":  # the grid halves down to at most 12 points per side
+        N = rng.choice([48, 64, 80, 96, 112, 128, 144, 160, 176, 192])
+    else:
+        N = _log_int(rng, 24, 192)
+    mixed = rng.random() < 0.5
+    c = dict(kind=kind, cells=max(2, int(round(N / inputs.GRID_PER_CELL))), N=N,
+             order=rng.choice([2, 2, 4]), mixed=mixed,
+             tol=rng.choice([1e-6, 1e-8] if mixed else [1e-8, 1e-9, 1e-10]), form=form)
+    if kind == "md":
+        c["langevin"] = rng.random() < 0.25
+    return c
+
+
+# ---- inputs ------------------------------------------------------------------
+LANGEVIN_GAMMA, LANGEVIN_T = 1e-3, 1550.0   # 1/fs, K (the paper's equilibration)
+STEP_FRAMES = 64                            # positions of the step case, one per pass
+
+
+def _system(case, seed):
+    if case.get("bcc"):
+        s = inputs.bcc_nacl(case["cells"], box=20.64, grid_spacing=20.64 / case["N"],
+                            temperature=LANGEVIN_T, seed=seed)
+        s.pos = s.pos + np.random.default_rng(seed + 1).standard_normal(s.pos.shape) * 0.1
+        return s
+    s = inputs.molten_nacl(case["cells"], seed=seed)
+    if "N" in case:
+        s.grid_spacing = s.box / case["N"]
+    return s
+
+
+def _members(case, seed):
+    """(system, mixed, tol) of each session of an ensemble or serve case:
+    sizes fixed by the case, configurations drawn from the seed."""
+    out = []
+    if case["kind"] == "ensemble":
+        for k, r in enumerate(inputs.ensemble_replicas(case["count"], case["draw_seed"])):
+            out.append((inputs.molten_nacl(r.n_cells, seed=seed * 1000 + k,
+                                           temperature=r.temperature),
+                        case["mixed"], case["tol"]))
+    else:
+        for k, d in enumerate(inputs.serving_sessions(case["count"], case["draw_seed"],
+                                                      max_cells=8)):
+            out.append((inputs.molten_nacl(d["n_cells"], seed=seed * 1000 + k), d["mixed"],
+                        d["tol"]))
+    return out
+
+
+def _dt(case):
+    return 0.25 if case.get("langevin") else 1.0
+
+
+def _precision(mixed):
+    return maze.MAZE_MIXED if mixed else maze.MAZE_FP64
+
+
+def _dev(a, dtype=torch.float64):
+    return torch.tensor(np.ascontiguousarray(a), dtype=dtype, device="cuda")
+
+
+class _Pool:
+    """MD sessions whose particle arrays are slices of shared tensors."""
+
+    def __init__(self, members, form):
+        n = [s.n_ions for s, _, _ in members]
+        at = np.concatenate([[0], np.cumsum(n)])
+        total = int(at[-1])
+        self.pos = _dev(np.concatenate([s.pos for s, _, _ in members]))
+        self.vel = _dev(np.concatenate([s.vel for s, _, _ in members]))
+        self.charges = _dev(np.concatenate([s.charges for s, _, _ in members]))
+        self.mass = _dev(np.concatenate([s.masses for s, _, _ in members]))
+        self.species = _dev(np.concatenate([s.species for s, _, _ in members]), torch.int32)
+        self.f_es = torch.zeros(total, 3, dtype=torch.float64, device="cuda")
+        self.f_sr = torch.zeros_like(self.f_es)
+        self.scalars = torch.zeros(len(members), 8, dtype=torch.float64, device="cuda")
+        self.scratch, self.sessions, self.mds = [], [], []
+        table = (maze.ctypes.c_double * 15)(*inputs.BMH_TABLE.ravel().tolist())
+        for i, (s, mixed, tol) in enumerate(members):
+            a, b = int(at[i]), int(at[i + 1])
+            m = n[i]
+            scratch = torch.zeros(6 * m + 8 * ((m + 255) // 256), dtype=torch.float64,
+                                  device="cuda")
+            sess = maze.Session(self.charges[a:b], self.pos[a:b], s.box, s.grid_spacing, tol=tol,
+                                precision=_precision(mixed), coulomb_k=inputs.COULOMB_K_EV_A,
+                                flags=FORMS[form])
+            st = maze.maze_md_state(
+                m, 0, self.pos[a:b].data_ptr(), self.vel[a:b].data_ptr(),
+                self.mass[a:b].data_ptr(), self.species[a:b].data_ptr(),
+                self.f_es[a:b].data_ptr(), self.f_sr[a:b].data_ptr(), scratch.data_ptr(),
+                self.scalars[i].data_ptr(), 1.0, inputs.ACCEL_FACTOR, inputs.BMH_CUTOFF, table,
+                0.0, 0.0, 0)
+            maze.maze_md_prime(sess.handle, st, want_stats=False)
+            self.scratch.append(scratch)
+            self.sessions.append(sess)
+            self.mds.append(st)
+        self.handles = [s.handle for s in self.sessions]
+
+    def outputs(self):
+        return dict(pos=self.pos, vel=self.vel, f_es=self.f_es, f_sr=self.f_sr,
+                    scalars=self.scalars)
+
+
+def prepare(case, seed):
+    kind = case["kind"]
+    if kind in ("ensemble", "serve"):
+        pool = _Pool(_members(case, seed), case["form"])
+        batch = maze.Batch(max_sessions=64) if kind == "serve" else None
+        return dict(kind=kind, pool=pool, batch=batch)
+    s = _system(case, seed)
+    if kind == "rdf":
+        pos = _dev(s.pos)
+        hist = observables.PairHistogram(_dev(s.species, torch.int32), s.box, case["r_max"],
+                                         case["nbins"],
+                                         stream=torch.cuda.current_stream().cuda_stream)
+        return dict(kind=kind, pos=pos, hist=hist)
+    if kind == "md":
+        run_ = md.MDRun(s, tol=case["tol"], precision=_precision(case["mixed"]),
+                        order=case["order"], dt=_dt(case), flags=FORMS[case["form"]],
+                        gamma=LANGEVIN_GAMMA if case["langevin"] else 0.0,
+                        temperature=LANGEVIN_T if case["langevin"] else 0.0, seed=seed)
+        return dict(kind=kind, run=run_)
+    sess = maze.Session(_dev(s.charges), _dev(s.pos), s.box, s.grid_spacing, tol=case["tol"],
+                        order=case["order"], precision=_precision(case["mixed"]),
+                        coulomb_k=inputs.COULOMB_K_EV_A, flags=FORMS[case["form"]])
+    if kind == "solve":
+        return dict(kind=kind, session=sess, pos=_dev(s.pos + s.vel))
+    frames = [_dev(_frame(s, k)) for k in range(STEP_FRAMES)]
+    return dict(kind=kind, session=sess, frames=frames, at=0)
+
+
+def _frame(s, k):
+    """Positions of pass k of a step case: a smooth oscillation whose largest
+    speed is the thermal one (1 fs per pass)."""
+    w = 2.0 * math.pi / STEP_FRAMES
+    return s.pos + s.vel * (math.sin(w * (k + 1)) / w)
+
+
+# ---- one pass ----------------------------------------------------------------
+def run(state):
+    kind = state["kind"]
+    if kind == "md":
+        r = state["run"]
+        r.step()
+        return dict(pos=r.pos, vel=r.vel, f_es=r.f_es, f_sr=r.f_sr, scalars=r.scalars)
+    if kind == "step":
+        pos = state["frames"][state["at"] % STEP_FRAMES]
+        state["at"] += 1
+        out = state["session"].step(pos, want_field=True, want_stats=False)
+        return dict(field=out["field"], forces=out["forces"], energy=out["energy"])
+    if kind == "solve":
+        out = state["session"].solve(state["pos"], guess=maze.MAZE_GUESS_ZERO)
+        return dict(field=out["field"], forces=out["forces"], energy=out["energy"])
+    if kind == "rdf":
+        state["hist"].accumulate(state["pos"])
+        return dict(hist=state["hist"].hist)
+    pool = state["pool"]
+    if kind == "ensemble":
+        maze.maze_md_step_batch(pool.handles, pool.mds)
+        return pool.outputs()
+    batch = state["batch"]
+    for tag, (h, m) in enumerate(zip(pool.handles, pool.mds)):
+        batch.add_md(h, m, tag)
+    done = 0
+    while done < len(pool.handles):
+        if batch.advance() > 0:
+            done += len(batch.take())
+    return pool.outputs()
+
+
+# ---- bytes and operations a pass cannot do without -----------------------------
+# A MaZe step reads phi^k, phi^{k-1} and y and writes phi^{k+1} and y; a
+# direct solve writes its field. Per ion an MD step reads position, velocity,
+# both forces, mass, charge and species and writes the first four. Operations:
+# the charge projection, extrapolation, one stencil and the update per point,
+# weights and differences per support point of an ion.
+def _grid_work(N, n, order, md_step, fields):
+    return (8.0 * fields * N ** 3 + n * ((12 + 12 + 2.5) * 8.0 if md_step else 7 * 8.0),
+            20.0 * N ** 3 + n * (order ** 3) * 20.0)
+
+
+def work(case):
+    kind = case["kind"]
+    if kind == "rdf":
+        n = 8 * case["cells"] ** 3
+        box = case["cells"] * inputs.LATTICE_A
+        pairs = 0.5 * n * n * (4.0 / 3.0 * math.pi * case["r_max"] ** 3) / box ** 3
+        return dict(bytes=28.0 * n + 3 * 8.0 * case["nbins"], flops=14.0 * pairs)
+    if kind in ("ensemble", "serve"):
+        b = f = 0.0
+        if kind == "ensemble":
+            cells = [r.n_cells for r in inputs.ensemble_replicas(case["count"],
+                                                                 case["draw_seed"])]
+        else:
+            cells = [d["n_cells"] for d in inputs.serving_sessions(case["count"],
+                                                                   case["draw_seed"],
+                                                                   max_cells=8)]
+        for c in cells:
+            bb, ff = _grid_work(16 * c, 8 * c ** 3, 2, True, 5)
+            b, f = b + bb, f + ff
+        return dict(bytes=b, flops=f)
+    n = (2 if case.get("bcc") else 8) * case["cells"] ** 3
+    b, f = _grid_work(case["N"], n, case["order"], kind == "md",
+                      {"md": 5, "step": 6, "solve": 1}[kind])
+    return dict(bytes=b, flops=f)
+
+
+# ---- the values in 64 bits, by FFT and direct sums -----------------------------
+def _weights(t, order):
+    if order == 2:
+        return torch.stack([1.0 - t, t], -1)
+
+    def b3(s):
+        a = s.abs()
+        return torch.where(a < 1.0, 2.0 / 3.0 - a * a + a ** 3 / 2.0, (2.0 - a) ** 3 / 6.0)
+    return torch.stack([b3(1.0 + t), b3(t), b3(1.0 - t), b3(2.0 - t)], -1)
+
+
+def _poisson(pos, Q, box, N, order, k):
+    """(field, forces, energy) of M phi = -4 pi q / h, mean zero."""
+    h = box / N
+    u = torch.remainder(pos, box) / h
+    c = torch.floor(u)
+    w = _weights(u - c, order)                                  # n, 3, order
+    off = torch.arange(order, device=pos.device) - (0 if order == 2 else 1)
+    idx = torch.remainder(c.long()[:, :, None] + off, N)        # n, 3, order
+    W = (w[:, 0, :, None, None] * w[:, 1, None, :, None] * w[:, 2, None, None, :])
+    X, Y, Z = idx[:, 0, :, None, None], idx[:, 1, None, :, None], idx[:, 2, None, None, :]
+    q = torch.zeros(N ** 3, dtype=torch.float64, device=pos.device)
+    q.index_add_(0, ((X * N + Y) * N + Z).reshape(-1), (Q[:, None, None, None] * W).reshape(-1))
+    q = q.view(N, N, N) - q.mean()
+    m = 2.0 - 2.0 * torch.cos(2.0 * math.pi * torch.arange(N, dtype=torch.float64,
+                                                           device=pos.device) / N)
+    lam = m[:, None, None] + m[None, :, None] + m[None, None, :N // 2 + 1]
+    lam[0, 0, 0] = 1.0
+    ft = torch.fft.rfftn(q) * (4.0 * math.pi / h) / lam
+    ft[0, 0, 0] = 0.0
+    phi = torch.fft.irfftn(ft, s=(N, N, N))
+    F = []
+    for d in range(3):
+        g = (torch.roll(phi, -1, d) - torch.roll(phi, 1, d)) / (2.0 * h)
+        F.append(-k * Q * (W * g[X, Y, Z]).sum((1, 2, 3)))
+    return phi, torch.stack(F, -1), 0.5 * k * (phi * q).sum()
+
+
+def _bmh(pos, species, box):
+    """Short-range forces and energy (shifted to zero at the cutoff)."""
+    tab = torch.tensor(inputs.BMH_TABLE, device=pos.device)
+    rc = inputs.BMH_CUTOFF
+
+    def v(t, r):
+        return t[..., 0] * torch.exp(t[..., 1] * (t[..., 2] - r)) - t[..., 3] / r ** 6 - t[..., 4] / r ** 8
+
+    shift = v(tab, torch.full((3,), rc, dtype=torch.float64, device=pos.device))
+    F, E, n = torch.zeros_like(pos), 0.0, pos.shape[0]
+    for a in range(0, n, 1024):
+        d = pos[a:a + 1024, None, :] - pos[None]
+        d -= box * torch.round(d / box)
+        r2 = (d * d).sum(-1)
+        i, j = torch.nonzero((r2 < rc * rc) & (r2 > 0), as_tuple=True)
+        dd, r = d[i, j], r2[i, j].sqrt()
+        t = (species[a + i] + species[j]).long()
+        T = tab[t]
+        dv = (-T[:, 0] * T[:, 1] * torch.exp(T[:, 1] * (T[:, 2] - r)) + 6.0 * T[:, 3] / r ** 7
+              + 8.0 * T[:, 4] / r ** 9)
+        F.index_add_(0, a + i, (-dv / r)[:, None] * dd)
+        E = E + 0.5 * (v(T, r) - shift[t]).sum()
+    return F, E
+
+
+def _philox(counter, key):
+    """Philox4x32-10 (Salmon, Moraes, Dror and Shaw, SC'11) on uint64 words."""
+    c = [np.asarray(x, dtype=np.uint64) for x in counter]
+    k0, k1 = key
+    M = np.uint64(0xFFFFFFFF)
+    for _ in range(10):
+        p0, p1 = np.uint64(0xD2511F53) * c[0], np.uint64(0xCD9E8D57) * c[2]
+        c = [(p1 >> np.uint64(32)) ^ c[1] ^ np.uint64(k0), p1 & M,
+             (p0 >> np.uint64(32)) ^ c[3] ^ np.uint64(k1), p0 & M]
+        k0, k1 = (k0 + 0x9E3779B9) & 0xFFFFFFFF, (k1 + 0xBB67AE85) & 0xFFFFFFFF
+    return c
+
+
+def _noise(seed, step, half, n):
+    i = np.arange(n, dtype=np.uint64)
+    z = np.zeros(n, dtype=np.uint64)
+    x = _philox([i, z + np.uint64(half), z + np.uint64(step & 0xFFFFFFFF),
+                 z + np.uint64(step >> 32)], (seed & 0xFFFFFFFF, seed >> 32))
+    s = 2.0 ** -32
+    r0, r1 = (np.sqrt(-2.0 * np.log((x[k].astype(float) + 1.0) * s)) for k in (0, 2))
+    t0, t1 = (2.0 * math.pi * x[k].astype(float) * s for k in (1, 3))
+    return np.stack([r0 * np.cos(t0), r0 * np.sin(t0), r1 * np.cos(t1)], -1)
+
+
+def _md_exact(s, dt, order, langevin, seed, dev):
+    def f64(a):
+        return torch.tensor(np.asarray(a), dtype=torch.float64, device=dev)
+    k, N = inputs.COULOMB_K_EV_A, int(round(s.box / s.grid_spacing))
+    pos, vel, Q, m = f64(s.pos), f64(s.vel), f64(s.charges), f64(s.masses)[:, None]
+    sp = torch.tensor(s.species, device=dev)
+
+    def forces(x):
+        _, fe, e = _poisson(x, Q, s.box, N, order, k)
+        fs, es = _bmh(x, sp, s.box)
+        return fe, fs, e, es
+
+    a = math.exp(-LANGEVIN_GAMMA * dt / 2.0) if langevin else 1.0
+    cs = torch.sqrt((1.0 - a * a) * inputs.KB_EV_PER_K * LANGEVIN_T * inputs.ACCEL_FACTOR / m)
+
+    def ou(v, half):  # step 1: the priming step was step 0
+        return a * v + cs * f64(_noise(seed, 1, half, s.n_ions)) if langevin else v
+
+    c = 0.5 * dt * inputs.ACCEL_FACTOR / m
+    fe0, fs0, _, _ = forces(pos)
+    v = ou(vel, 0) + c * (fe0 + fs0)
+    x = pos + dt * v
+    fe, fs, e, es = forces(x)
+    v = ou(v + c * (fe + fs), 1)
+    w = (0.5 * (fe0 + fe) * (x - pos)).sum()
+    ke = (0.5 * m * v * v).sum() / inputs.ACCEL_FACTOR
+    z = torch.zeros((), dtype=torch.float64, device=dev)
+    es = es if isinstance(es, torch.Tensor) else z
+    sc = torch.stack([-w, es, ke, *(m * v).sum(0), e, z])
+    return dict(pos=x, vel=v, f_es=fe, f_sr=fs, scalars=sc)
+
+
+def exact(case, seed):
+    dev = "cuda" if torch.cuda.is_available() else "cpu"
+    kind = case["kind"]
+    if kind == "rdf":
+        return None  # counts: equal or not
+    if kind in ("ensemble", "serve"):
+        got = [_md_exact(s, 1.0, 2, False, seed, dev) for s, _, _ in _members(case, seed)]
+        out = {k: torch.cat([g[k] for g in got]) for k in ("pos", "vel", "f_es", "f_sr")}
+        out["scalars"] = torch.stack([g["scalars"] for g in got])
+        return out
+    s = _system(case, seed)
+    if kind == "md":
+        return _md_exact(s, _dt(case), case["order"], case["langevin"], seed, dev)
+    pos = s.pos + s.vel if kind == "solve" else _frame(s, 0)
+    f = torch.tensor(pos, dtype=torch.float64, device=dev)
+    q = torch.tensor(s.charges, dtype=torch.float64, device=dev)
+    phi, F, e = _poisson(f, q, s.box, case["N"], case["order"], inputs.COULOMB_K_EV_A)
+    return dict(field=phi, forces=F, energy=e.reshape(1))
