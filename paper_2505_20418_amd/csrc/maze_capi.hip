@@ -52,6 +52,8 @@ struct maze_session {
   SweepGeom sweep{};     // latency shape: alone and in batches below the fill level
   SweepGeom sweep_tp{};  // throughput shape: batches that fill the GPU
   SweepGeom sbasis{};    // basis kernel of the two-iteration CG (own shape)
+  PersistGeom pgeom{};   // resident solves; nwg = 0: solved by launched sweeps
+  int president = 0;     // workgroups of a batched resident launch that fit the device
   hipStream_t stream = nullptr;
   // captured chunks of kPollBatch sweeps, [fp32][parity of the first sweep]
   // [slot]: a graph holds its kernels' arguments, and the solution vector
@@ -199,6 +201,15 @@ static int part_stride_for(const DeviceState& d, const MarchGeom& g, const Sweep
   return m;
 }
 
+// Resident form of a session's solves: the one-iteration Jacobi PLCG on grids
+// whose vectors fit on the chip. MAZE_PERSIST=0 in the environment keeps to
+// launched sweeps.
+static PersistGeom persist_geom_of(const maze_config* c, int N) {
+  const char* e = std::getenv("MAZE_PERSIST");
+  if ((e && e[0] == '0') || (c->flags & (MAZE_FLAG_MULTIGRID | MAZE_FLAG_SSTEP))) return {};
+  return make_persist_geom(N, c->precision == MAZE_MIXED);
+}
+
 struct Layout {
   size_t off[64];
   size_t total = 0;
@@ -254,14 +265,15 @@ static Layout layout_for(const maze_config* c, int N, int* ntx_out, int* ntiles_
   L.add(sizeof(double) * (n + 1));        // 23 md_epart
   L.add(sizeof(double) * kHistCap);       // 24 residual history
   L.add(sizeof(int32_t) * (size_t)ntx * (1 + kMaxCandAxis));  // 25 spreading candidates
+  L.add(persist_bytes(persist_geom_of(c, N), mixed));          // 26 resident solves
   if (mg) {
     int Ns[kMgMaxLevels];
     const int levels = mg_plan(N, Ns, kMgMaxLevels);
     const size_t es = (c->precision == MAZE_MIXED) ? sizeof(float) : sizeof(double);
     const bool f32 = es == sizeof(float);
-    L.add(f32 ? es * (size_t)G : 0);  // 26 z (FP64 uses the second r buffer)
-    L.add(f32 ? es * (size_t)G : 0);  // 27 rounded level-0 right-hand side
-    L.add(es * (size_t)G);            // 28 level-0 residual
+    L.add(f32 ? es * (size_t)G : 0);  // 27 z (FP64 uses the second r buffer)
+    L.add(f32 ? es * (size_t)G : 0);  // 28 rounded level-0 right-hand side
+    L.add(es * (size_t)G);            // 29 level-0 residual
     for (int l = 1; l < levels; ++l) {
       const size_t gl = (size_t)Ns[l] * Ns[l] * Ns[l];
       L.add(es * gl);  // x_l
@@ -621,6 +633,11 @@ static int gather_scalars(std::vector<maze_session*>& ss, std::vector<Scalars>& 
 // the environment forces one mode.
 constexpr long long kThroughputWgs = 256;
 
+static bool batch_mode_forced() {
+  const char* e = std::getenv("MAZE_BATCH_MODE");
+  return e && (std::strcmp(e, "latency") == 0 || std::strcmp(e, "throughput") == 0);
+}
+
 static bool batch_throughput_mode(const std::vector<CgJob>& jobs) {
   const char* e = std::getenv("MAZE_BATCH_MODE");
   if (e && std::strcmp(e, "latency") == 0) return false;
@@ -744,6 +761,161 @@ static int batch_loop(std::vector<CgJob>& jobs, const std::vector<int>& order, B
 
 static int run_sstep_batch(std::vector<CgJob>& jobs, bool fp32, bool zero_x, int first_batch);
 
+// ---- resident solves -----------------------------------------------------------
+// The workgroups of a resident solve wait for each other, so two of them must
+// not share a device half started. The launches of one process are kept
+// apart: a call that waits for its solve holds the device's gate until the
+// solve has ended, and a continuous batch, which does not wait, leaves an
+// event that launches on other streams wait for. Another process's kernels
+// can still delay a solve past its bounded waits: it then ends as kErrAborted
+// and is repeated by launched sweeps.
+struct PersistGate {
+  std::mutex mu;
+  hipEvent_t ev = nullptr;       // the last solve nobody has waited for
+  hipStream_t stream = nullptr;  // its stream
+  bool pending = false;
+};
+static PersistGate g_gate[64];
+
+// Polls after which a workgroup gives up (about 1 us each).
+// MAZE_PERSIST_SPIN in the environment sets it (0: every solve is repeated
+// by launched sweeps).
+static unsigned persist_spin() {
+  const char* e = std::getenv("MAZE_PERSIST_SPIN");
+  return e ? (unsigned)std::strtoul(e, nullptr, 10) : 1u << 21;
+}
+
+static hipError_t gate_enter(PersistGate& g, hipStream_t st) {
+  if (!g.pending || g.stream == st) return hipSuccess;
+  return hipStreamWaitEvent(st, g.ev, 0);
+}
+
+// Whether a session's next solve runs in the resident form (timed sweeps are
+// launched ones).
+static bool persist_of(const maze_session* s) { return s->pgeom.nwg > 0 && !s->prof; }
+
+// Whether the resident solves of `ss` together take less time than one
+// batched solve of them by launched sweeps. Resident solves run (nearly) one
+// after the other, each at the latency of its exchange; a batched sweep moves
+// every session's bytes at the copy rate, with some 12 us per launch and class
+// as its floor. Iteration counts grow as N. Measured: 16 sessions of 32^3 to
+// 128^3, half FP64, 13.6 ms against 24.2 ms launched; 64 mixed replicas of
+// 32^3 to 96^3 51.0 ms against 34.9 ms, so the line lies between; the
+// estimates of the two cases are 7.2 against 13.5 and 23 against 14.5.
+static bool persist_pays(const std::vector<const maze_session*>& ss) {
+  double res = 0, bytes = 0;
+  int nmax = 0;
+  bool f32 = false, f64 = false;
+  for (const maze_session* s : ss) {
+    const bool mixed = s->cfg.precision == MAZE_MIXED;
+    (mixed ? f32 : f64) = true;
+    nmax = std::max(nmax, s->d.N);
+    res += (double)s->d.N * s->pgeom.cost_us;
+    bytes += (double)s->d.N * (double)s->d.G * (mixed ? 24.0 : 48.0);
+  }
+  return res <= bytes / 5.0e6 + 12.0 * nmax * (1 + (f32 ? 1 : 0) + (f64 ? 1 : 0));
+}
+
+// Queues the resident solves `idx` of jobs (sessions and solution vectors
+// through `job`) on st: one session directly; several of the smaller
+// classes from the table (args,
+// geometries and workgroup prefixes, uploaded here), as many per launch as
+// are resident together.
+template <class F>
+static int queue_persist(const std::vector<int>& idx, F job, bool fp32, bool zero_x, BatchTable* t,
+                         hipStream_t st) {
+  const unsigned spin = persist_spin();
+  std::vector<int> order;
+  for (int i : idx)
+    if (idx.size() > 1 && persist_batched(job(i).s->pgeom)) order.push_back(i);
+  for (int i : idx) {
+    const CgJob j = job(i);
+    if (idx.size() > 1 && persist_batched(j.s->pgeom)) continue;
+    HIP_TRY(launch_persist(j.s->d, j.s->pgeom, j.x, fp32, zero_x, j.s->geom.nwg, spin, st));
+  }
+  if (order.empty()) return MAZE_OK;
+  std::stable_sort(order.begin(), order.end(),
+                   [&](int a, int b) { return job(a).s->pgeom.cls < job(b).s->pgeom.cls; });
+  struct Grp { int c0, c1, wgb0, nwg, cls, cap; size_t lds; };
+  std::vector<Grp> grps;
+  char* H = t->host;
+  PersistGeom* hg = (PersistGeom*)(H + t->o_geom);
+  int* hw = (int*)(H + t->o_wgb);
+  int wpos = 0;
+  for (int q = 0; q < (int)order.size(); ++q) {
+    const CgJob j = job(order[q]);
+    maze_session* s = j.s;
+    const PersistGeom& g = s->pgeom;
+    const size_t lds = persist_lds_bytes(g, fp32);
+    // the members' own capacity bounds a launch (a larger brick's LDS and
+    // registers hold fewer workgroups per CU)
+    if (grps.empty() || grps.back().cls != g.cls ||
+        grps.back().nwg + g.nwg > std::min(grps.back().cap, s->president)) {
+      if (!grps.empty()) hw[wpos++] = grps.back().nwg;
+      grps.push_back({q, q, wpos, 0, g.cls, s->president, 0});
+    }
+    Grp& G = grps.back();
+    hw[wpos++] = G.nwg;
+    G.nwg += g.nwg;
+    G.c1 = q + 1;
+    G.cap = std::min(G.cap, s->president);
+    G.lds = std::max(G.lds, lds);
+    hg[q] = g;
+    if (fp32)
+      ((SweepArgs<float>*)(H + t->o_args))[q] =
+          make_sweep_args<float>(s->d, (float*)j.x, s->geom.nwg, 0, zero_x);
+    else
+      ((SweepArgs<double>*)(H + t->o_args))[q] =
+          make_sweep_args<double>(s->d, (double*)j.x, s->geom.nwg, 0, zero_x);
+  }
+  hw[wpos++] = grps.back().nwg;
+  HIP_TRY(hipMemcpyAsync(t->dev, H, t->o_geom2, hipMemcpyHostToDevice, st));
+  for (const Grp& G : grps)
+    HIP_TRY(launch_persist_batch(t->dev + t->o_args + (size_t)G.c0 * sizeof(SweepArgs<double>),
+                                 (const PersistGeom*)(t->dev + t->o_geom) + G.c0,
+                                 (const int*)(t->dev + t->o_wgb) + G.wgb0, G.c1 - G.c0, G.nwg,
+                                 G.cls, G.lds, fp32, spin, st));
+  return MAZE_OK;
+}
+static_assert(sizeof(PersistGeom) <= sizeof(SweepGeom), "the batch table's geometry array");
+
+// Runs the jobs' solves in the resident form and waits for them. A solve
+// that gave up waiting comes back with err = kErrAborted.
+static int run_persist(std::vector<CgJob>& jobs, bool fp32, bool zero_x) {
+  const int n = (int)jobs.size();
+  const int device = jobs[0].s->device;
+  if (device < 0 || device >= 64) return MAZE_E_DEVICE;
+  hipStream_t st = jobs[0].s->stream;
+  BatchTable* t = nullptr;
+  if (n > 1) {
+    const int rc = ensure_table(device, n, &t);
+    if (rc != MAZE_OK) return rc;
+  }
+  std::vector<int> idx(n);
+  for (int i = 0; i < n; ++i) idx[i] = i;
+  std::vector<maze_session*> ss(n);
+  for (int i = 0; i < n; ++i) ss[i] = jobs[i].s;
+  std::vector<Scalars> h;
+  {
+    PersistGate& g = g_gate[device];
+    std::lock_guard<std::mutex> lk(g.mu);
+    HIP_TRY(gate_enter(g, st));
+    int rc = queue_persist(idx, [&](int i) -> const CgJob& { return jobs[i]; }, fp32, zero_x, t, st);
+    if (rc == MAZE_OK) rc = gather_scalars(ss, h);
+    if (rc != MAZE_OK) return rc;
+  }
+  for (int i = 0; i < n; ++i) {
+    jobs[i].err = h[i].err;
+    jobs[i].iters = h[i].iters;
+    jobs[i].code = h[i].done ? h[i].done : 3;
+    if (!jobs[i].err && ss[i]->trace) {
+      const int rc = trace_collect(ss[i], jobs[i].iters, h[i].qnorm);
+      if (rc != MAZE_OK) return rc;
+    }
+  }
+  return MAZE_OK;
+}
+
 // Batched solves replay their poll groups from captured graphs when every
 // session asks for graph chunks (MAZE_FLAG_GRAPH_CHUNKS), the stream can be
 // captured and no session samples its timing.
@@ -756,8 +928,31 @@ static bool batch_graphs(const std::vector<CgJob>& jobs, hipStream_t st) {
 
 // Batched CG solves: one launch per sweep and template class covers every
 // session; a compact status array is polled.
-static int run_cg_batch(std::vector<CgJob>& jobs, bool fp32, bool zero_x, int first_batch) {
+// launched: no resident solves (the choice has been made).
+static int run_cg_batch(std::vector<CgJob>& jobs, bool fp32, bool zero_x, int first_batch,
+                        bool launched = false) {
   const int n = (int)jobs.size();
+  // resident solves on their own
+  if (!launched) {
+    std::vector<CgJob> res, rest;
+    std::vector<const maze_session*> rs;
+    for (const CgJob& j : jobs) {
+      (persist_of(j.s) ? res : rest).push_back(j);
+      if (persist_of(j.s)) rs.push_back(j.s);
+    }
+    // in the throughput shapes (results summed in another order than alone)
+    // only where that is the faster form
+    const bool pays = n == 1 || !batch_throughput_mode(jobs) ||
+                      (!batch_mode_forced() && persist_pays(rs));
+    if (!res.empty() && pays) {
+      int rc = run_persist(res, fp32, zero_x);
+      if (rc == MAZE_OK && !rest.empty()) rc = run_cg_batch(rest, fp32, zero_x, first_batch);
+      if (rc != MAZE_OK) return rc;
+      size_t a = 0, b = 0;  // results back into the caller's order
+      for (CgJob& j : jobs) j = persist_of(j.s) ? res[a++] : rest[b++];
+      return MAZE_OK;
+    }
+  }
   if (n == 1) return run_cg(jobs[0], fp32, zero_x, first_batch);
   // two-iteration sessions run in batches of their own
   {
@@ -766,9 +961,9 @@ static int run_cg_batch(std::vector<CgJob>& jobs, bool fp32, bool zero_x, int fi
     if (!ss.empty()) {
       int rc = MAZE_OK;
       if (one.empty()) return run_sstep_batch(jobs, fp32, zero_x, first_batch);
-      rc = run_cg_batch(one, fp32, zero_x, first_batch);
+      rc = run_cg_batch(one, fp32, zero_x, first_batch, true);
       if (rc != MAZE_OK) return rc;
-      rc = run_cg_batch(ss, fp32, zero_x, first_batch);
+      rc = run_cg_batch(ss, fp32, zero_x, first_batch, true);
       if (rc != MAZE_OK) return rc;
       size_t a = 0, b = 0;  // results back into the caller's order
       for (CgJob& j : jobs) j = sstep_of(j.s) ? ss[b++] : one[a++];
@@ -1028,6 +1223,20 @@ static int recover_error(maze_session* s) {
   return MAZE_E_NONFINITE;
 }
 
+// A solve's outcome by its error flag: rejected positions, or a resident
+// solve that gave up waiting (kRepeat, internal: the caller repeats it).
+constexpr int kRepeat = 1 << 20;
+static int solve_error(int err) { return err == kErrAborted ? kRepeat : MAZE_E_NONFINITE; }
+
+// Makes a session whose resident solve gave up ready for its repetition:
+// launched sweeps from here on, the error flag cleared.
+static int persist_off(maze_session* s) {
+  s->pgeom.nwg = 0;
+  HIP_TRY(hipStreamSynchronize(s->stream));
+  HIP_TRY(hipMemsetAsync(&s->d.sc->err, 0, sizeof(int32_t), s->stream));
+  return MAZE_OK;
+}
+
 // Solves M x = s for every session (s in d.sigma, the first residual and its
 // partials written by a right-hand-side kernel, thresholds set by
 // FIN_SOLVE_START). Sessions of one precision are solved together. Leaves
@@ -1087,7 +1296,7 @@ static int solve_multi(std::vector<maze_session*>& ss, std::vector<double*>& xs,
       for (size_t q = 0; q < jobs.size(); ++q) {
         maze_session* s = jobs[q].s;
         if (jobs[q].err) {
-          rcs[idx[q]] = MAZE_E_NONFINITE;
+          rcs[idx[q]] = solve_error(jobs[q].err);
           continue;
         }
         s->iters = jobs[q].iters;
@@ -1114,7 +1323,7 @@ static int solve_multi(std::vector<maze_session*>& ss, std::vector<double*>& xs,
     maze_session* s = ss[i];
     *more = false;
     if (j.err) {
-      rcs[i] = MAZE_E_NONFINITE;
+      rcs[i] = solve_error(j.err);
       return MAZE_OK;
     }
     const int it = j.iters;
@@ -1290,19 +1499,34 @@ static int direct_solve(maze_session* s, int guess, const double* pos, double* x
   const bool mixed = s->cfg.precision == MAZE_MIXED;
   int rc = assign(s, pos);
   if (rc != MAZE_OK) return rc;
-  HIP_TRY(launch_rhs_poisson(d, s->geom, guess, x, mixed && d.mg.levels == 0, s->stream));
-  HIP_TRY(launch_finalize(d, FIN_SOLVE_START, s->geom.nwg, s->cfg.tol, 0.0, 0.0, nullptr,
-                          s->cfg.max_iter, s->cfg.residual_norm, s->stream));
   std::vector<maze_session*> one{s};
   std::vector<double*> xs{x};
   std::vector<int> rcs;
-  rc = solve_multi(one, xs, rcs);
-  if (rc != MAZE_OK) return rc;
+  for (;;) {
+    HIP_TRY(launch_rhs_poisson(d, s->geom, guess, x, mixed && d.mg.levels == 0, s->stream));
+    HIP_TRY(launch_finalize(d, FIN_SOLVE_START, s->geom.nwg, s->cfg.tol, 0.0, 0.0, nullptr,
+                            s->cfg.max_iter, s->cfg.residual_norm, s->stream));
+    rc = solve_multi(one, xs, rcs);
+    if (rc != MAZE_OK) return rc;
+    if (rcs[0] != kRepeat) break;
+    rc = persist_off(s);
+    if (rc != MAZE_OK) return rc;
+  }
   if (rcs[0] == MAZE_E_NONFINITE) return recover_error(s);
   HIP_TRY(launch_project(d, x, field, s->stream));
   HIP_TRY(launch_finalize(d, FIN_ENERGY, update_blocks(d.G), 0.0, 0.0, s->cfg.coulomb_k,
                           energy, 0, 0, s->stream));
   if (forces) HIP_TRY(launch_gather(d, x, s->cfg.coulomb_k, forces, s->stream));
+  return MAZE_OK;
+}
+
+// Right-hand side, first residual and thresholds of a MaZe step.
+static int step_rhs(maze_session* s) {
+  DeviceState& d = s->d;
+  HIP_TRY(launch_rhs_maze(d, s->geom, s->cfg.precision == MAZE_MIXED && d.mg.levels == 0,
+                          s->stream));
+  HIP_TRY(launch_finalize(d, FIN_SOLVE_START, s->geom.nwg, s->cfg.tol, 0.0, 0.0, nullptr,
+                          s->cfg.max_iter, s->cfg.residual_norm, s->stream));
   return MAZE_OK;
 }
 
@@ -1314,18 +1538,34 @@ static int step_multi(std::vector<maze_session*>& ss, const double* const* pos,
   const int n = (int)ss.size();
   std::vector<double*> ys(n);
   for (int i = 0; i < n; ++i) {
-    maze_session* s = ss[i];
-    DeviceState& d = s->d;
-    const int rc = assign(s, pos[i]);
+    const int rc = assign(ss[i], pos[i]);
     if (rc != MAZE_OK) return rc;
-    HIP_TRY(launch_rhs_maze(d, s->geom, s->cfg.precision == MAZE_MIXED && d.mg.levels == 0,
-                            s->stream));
-    HIP_TRY(launch_finalize(d, FIN_SOLVE_START, s->geom.nwg, s->cfg.tol, 0.0, 0.0, nullptr,
-                            s->cfg.max_iter, s->cfg.residual_norm, s->stream));
-    ys[i] = d.y;
+    const int rc2 = step_rhs(ss[i]);
+    if (rc2 != MAZE_OK) return rc2;
+    ys[i] = ss[i]->d.y;
   }
   int rc = solve_multi(ss, ys, rcs);
   if (rc != MAZE_OK) return rc;
+  // resident solves that gave up waiting: again, by launched sweeps, from the
+  // y that is there
+  std::vector<maze_session*> again;
+  std::vector<double*> again_y;
+  std::vector<int> again_rcs;
+  for (int i = 0; i < n; ++i) {
+    if (rcs[i] != kRepeat) continue;
+    rc = persist_off(ss[i]);
+    if (rc == MAZE_OK) rc = step_rhs(ss[i]);
+    if (rc != MAZE_OK) return rc;
+    again.push_back(ss[i]);
+    again_y.push_back(ys[i]);
+  }
+  if (!again.empty()) {
+    rc = solve_multi(again, again_y, again_rcs);
+    if (rc != MAZE_OK) return rc;
+    size_t q = 0;
+    for (int i = 0; i < n; ++i)
+      if (rcs[i] == kRepeat) rcs[i] = again_rcs[q++];
+  }
   for (int i = 0; i < n; ++i) {
     maze_session* s = ss[i];
     DeviceState& d = s->d;
@@ -1762,6 +2002,8 @@ struct BatchJob {
   double thr = 0.0;
   bool stop = false;       // mixed: a pass broke down without progress
   bool tp = false;         // the solve in flight runs in the throughput shapes
+  int res = 0;             // resident form: 1 to be queued, 2 queued
+  bool zero_x = false;     // resident form: the solve starts from x = 0
 };
 
 struct BatchLaunch {
@@ -1787,6 +2029,10 @@ struct maze_batch {
   bool dirty = true;
   std::vector<BatchLaunch> launches;
   std::vector<int> members;  // jobs in the current table, in table order
+  // tables of resident solves, used alternately by maze_batch_advance: the poll
+  // behind a table's launches has completed when its turn comes again
+  BatchTable rtab[2];
+  int rtab_cur = 0;
   long long unit = 0;        // batched units issued (their parity)
   // polls, double-buffered: device list of scalar pointers, device and
   // pinned host copies of the scalars
@@ -1826,7 +2072,20 @@ bool batch_solve_tp(const maze_batch* b, const maze_session* s) {
 int batch_first_unit(maze_batch* b, BatchJob& j, bool zero_x) {
   maze_session* s = j.s;
   j.tp = batch_solve_tp(b, s);
-  if (!j.tp) {
+  j.res = 0;
+  bool res = persist_of(s);
+  if (res && j.tp) {
+    std::vector<const maze_session*> ss{s};
+    for (const BatchJob& o : b->jobs)
+      if (o.phase == kBatchCg && o.s != s && persist_of(o.s)) ss.push_back(o.s);
+    res = !batch_mode_forced() && persist_pays(ss);
+  }
+  if (res) {
+    j.tp = false;
+    // queued by the next maze_batch_advance together with the others
+    j.res = 1;
+    j.zero_x = zero_x;
+  } else if (!j.tp) {
     HIP_TRY(launch_unit(s, 0, j.x, j.fp32, zero_x));
   } else if (sstep_of(s)) {
     HIP_TRY(launch_sstep_outer(s->d, s->sweep_tp, s->sweep_tp, 0, j.x, j.fp32, zero_x, s->stream));
@@ -1873,7 +2132,8 @@ int batch_rebuild(maze_batch* b) {
   b->launches.clear();
   b->members.clear();
   for (int i = 0; i < (int)b->jobs.size(); ++i)
-    if (b->jobs[i].phase == kBatchCg && b->jobs[i].rc == MAZE_OK) b->members.push_back(i);
+    if (b->jobs[i].phase == kBatchCg && b->jobs[i].rc == MAZE_OK && !b->jobs[i].res)
+      b->members.push_back(i);
   b->dirty = false;
   if (b->members.empty()) return MAZE_OK;
   auto job = [&](int q) -> BatchJob& { return b->jobs[b->members[q]]; };
@@ -2008,6 +2268,46 @@ int batch_unit(maze_batch* b) {
   return MAZE_OK;
 }
 
+// Queues the resident solves that wait to be queued.
+int batch_queue_resident(maze_batch* b, bool* any) {
+  *any = false;
+  for (int f = 0; f < 2; ++f)
+    for (int z = 0; z < 2; ++z) {
+      std::vector<int> idx;
+      for (int i = 0; i < (int)b->jobs.size(); ++i) {
+        BatchJob& j = b->jobs[i];
+        if (j.phase == kBatchCg && j.res == 1 && j.fp32 == (f == 1) && j.zero_x == (z == 1))
+          idx.push_back(i);
+      }
+      if (idx.empty()) continue;
+      if (*any) return MAZE_OK;  // one table per poll: the others' turn comes with the next
+      *any = true;
+      PersistGate& g = g_gate[b->device];
+      std::lock_guard<std::mutex> lk(g.mu);
+      if (!g.ev) HIP_TRY(hipEventCreateWithFlags(&g.ev, hipEventDisableTiming));
+      HIP_TRY(gate_enter(g, b->stream));
+      b->rtab_cur ^= 1;
+      const int rc = queue_persist(
+          idx,
+          [&](int i) {
+            CgJob j{};
+            j.s = b->jobs[i].s;
+            j.x = b->jobs[i].x;
+            return j;
+          },
+          f == 1, z == 1, &b->rtab[b->rtab_cur], b->stream);
+      if (rc != MAZE_OK) return rc;
+      HIP_TRY(hipEventRecord(g.ev, b->stream));
+      g.stream = b->stream;
+      g.pending = true;
+      for (int i : idx) {
+        b->jobs[i].res = 2;
+        b->jobs[i].ready = b->polls;
+      }
+    }
+  return MAZE_OK;
+}
+
 // Queues a copy of the scalars of every job in flight into poll slot
 // polls % 2.
 int batch_queue_poll(maze_batch* b) {
@@ -2044,6 +2344,25 @@ int batch_process(maze_batch* b, const maze_batch::Poll& P) {
     }
     const Scalars& h = *it->second;
     maze_session* s = j.s;
+    if (j.phase == kBatchCg && j.res == 1) {  // not queued yet
+      keep.push_back(j);
+      continue;
+    }
+    if (h.err == kErrAborted) {
+      // a resident solve gave up waiting: the step's solve again, launched
+      int rc = persist_off(s);
+      if (rc == MAZE_OK) rc = step_rhs(s);
+      if (rc != MAZE_OK) return rc;
+      if (j.fp32) {
+        j.phase = kBatchCheck;
+        j.ready = next_poll;
+      } else {
+        rc = batch_first_unit(b, j, false);
+        if (rc != MAZE_OK) return rc;
+      }
+      keep.push_back(j);
+      continue;
+    }
     if (h.err) {
       // a rejected position: nothing was advanced beyond the MD drift
       const int rc = recover_error(s);
@@ -2261,6 +2580,8 @@ int maze_init(const maze_config* cfg, const double* charges_dev, const double* p
   d.hist = (double*)at(24);
   d.hist_cap = kHistCap;
   d.cand = (int32_t*)at(25);
+  s->pgeom = persist_geom_of(cfg, d.N);
+  d.res = s->pgeom.nwg > 0 ? (char*)at(26) : nullptr;
   d.weight_gradient_force = (cfg->flags & MAZE_FLAG_WEIGHT_GRADIENT_FORCE) ? 1 : 0;
   if (mg) {
     MgHierarchy& m = d.mg;
@@ -2272,13 +2593,13 @@ int maze_init(const maze_config* cfg, const double* charges_dev, const double* p
       m.G[l] = (long long)Ns[l] * Ns[l] * Ns[l];
       m.c[l] = std::pow(0.25, l);
     }
-    m.z = m.fp32 ? at(26) : (void*)(d.r + d.G);
-    m.b[0] = m.fp32 ? at(27) : nullptr;
-    m.r[0] = at(28);
+    m.z = m.fp32 ? at(27) : (void*)(d.r + d.G);
+    m.b[0] = m.fp32 ? at(28) : nullptr;
+    m.r[0] = at(29);
     for (int l = 1; l < m.levels; ++l) {
-      m.x[l] = at(29 + 3 * (l - 1));
-      m.b[l] = at(30 + 3 * (l - 1));
-      m.r[l] = at(31 + 3 * (l - 1));
+      m.x[l] = at(30 + 3 * (l - 1));
+      m.b[l] = at(31 + 3 * (l - 1));
+      m.r[l] = at(32 + 3 * (l - 1));
     }
   }
   if (hipHostMalloc((void**)&s->host_sc, 2 * sizeof(Scalars), hipHostMallocDefault) !=
@@ -2298,6 +2619,16 @@ int maze_init(const maze_config* cfg, const double* charges_dev, const double* p
   // launch shape of the CG sweep (timed on the still-unused buffers), then
   // clear them again for the first solve
   s->sweep = autotune_sweep(s);
+  SweepGeom forced;
+  if (forced_shape(d, mixed, &forced)) s->pgeom.nwg = 0;  // a forced shape is a launched sweep's
+  if (s->pgeom.nwg > 0) {
+    const int cus = device_cus();
+    const bool batched = persist_batched(s->pgeom);
+    s->president = batched ? persist_resident(s->pgeom, mixed, true, cus) : 0;
+    if ((batched && s->president < s->pgeom.nwg) ||
+        persist_resident(s->pgeom, mixed, false, cus) < s->pgeom.nwg)
+      s->pgeom.nwg = 0;
+  }
   s->sweep_tp = throughput_sweep(s->d, s->cfg.precision == MAZE_MIXED);
   if (sstep_of(s)) {
     // the two-iteration kernels stage one more array in LDS than the sweep:
@@ -2324,7 +2655,8 @@ int maze_init(const maze_config* cfg, const double* charges_dev, const double* p
   if (hipMemsetAsync(base, 0, L.total, stream) != hipSuccess ||
       hipMemcpyAsync(d.Q, charges_dev, sizeof(double) * n, hipMemcpyDeviceToDevice, stream) !=
           hipSuccess ||
-      launch_cand_table(d, stream) != hipSuccess) {
+      launch_cand_table(d, stream) != hipSuccess ||
+      (s->pgeom.nwg > 0 && launch_persist_empty(d, s->pgeom, mixed, stream) != hipSuccess)) {
     maze_destroy(s);
     return MAZE_E_DEVICE;
   }
@@ -2690,7 +3022,8 @@ int maze_batch_create(void* stream, int32_t max_sessions, maze_batch** out) {
   b->cap = max_sessions;
   hipGetDevice(&b->device);
   bool ok = true;
-  for (BatchTable& t : b->tab) {
+  for (BatchTable* pt : {&b->tab[0], &b->tab[1], &b->rtab[0], &b->rtab[1]}) {
+    BatchTable& t = *pt;
     t = table_layout(max_sessions);
     ok = ok && hipMalloc((void**)&t.dev, t.bytes) == hipSuccess &&
          hipHostMalloc((void**)&t.host, t.bytes, hipHostMallocDefault) == hipSuccess;
@@ -2770,8 +3103,14 @@ int maze_batch_advance(maze_batch* b, int32_t* n_ready) {
     const int rc = batch_rebuild(b);
     if (rc != MAZE_OK) return rc;
   }
-  const bool running = !b->members.empty();
-  if (running) {
+  bool resident = false;
+  {
+    const int rc = batch_queue_resident(b, &resident);
+    if (rc != MAZE_OK) return rc;
+  }
+  const bool launched = !b->members.empty();
+  const bool running = launched || resident;
+  if (launched) {
     // one poll per kPollBatch sweeps or half as many two-iteration units:
     // a unit covers every running solve, and units queued after a solve has
     // ended return at once
@@ -2830,9 +3169,9 @@ void maze_batch_destroy(maze_batch* b) {
     if (maze_batch_advance(b, nullptr) != MAZE_OK) break;
   if (b->stream) hipStreamSynchronize(b->stream);
   else hipDeviceSynchronize();
-  for (BatchTable& t : b->tab) {
-    if (t.dev) hipFree(t.dev);
-    if (t.host) hipHostFree(t.host);
+  for (BatchTable* t : {&b->tab[0], &b->tab[1], &b->rtab[0], &b->rtab[1]}) {
+    if (t->dev) hipFree(t->dev);
+    if (t->host) hipHostFree(t->host);
   }
   for (maze_batch::Poll& P : b->poll) {
     if (P.dev) hipFree(P.dev);

@@ -75,7 +75,9 @@ struct alignas(64) Scalars {
   double mg_beta;      // rho / rho of the previous iteration (0 first)
   double thr_outer;    // mixed step: the step's threshold, kept by
                        // FIN_INNER_FIRST while thr holds the inner one
-  double pad[1];
+  int32_t res_iter;    // resident solves: iterations so far, mod 12 (the period
+                       // of their exchange sets)
+  int32_t pad;
 };
 
 // Geometry of a marching stencil launch: each workgroup owns a contiguous
@@ -117,6 +119,29 @@ struct SweepGeom {
 
 SweepGeom make_sweep_geom(int N, int ppt, int cx);
 size_t sweep_lds_bytes(const SweepGeom& g, bool fp32, bool first);
+
+// Resident solves (k_persist.hip): one workgroup per brick of the grid, whole
+// rows in z; ncx x ncy bricks split N as evenly as possible.
+constexpr int kPersistMaxWg = 256;
+constexpr int kPersistSweepSums = 5;   // sums that the workgroups exchange
+constexpr int kPersistRed = 128;       // doubles of LDS for a reduction
+constexpr size_t kPersistMaxLds = 160 * 1024 - 2048;
+// exchange slots: four sets of sums, one 64-byte line per workgroup
+constexpr int kPersistSlots = 4 * 8 * kPersistMaxWg;
+constexpr size_t kPersistSlotBytes = sizeof(double) * kPersistSlots;
+// contents of an empty slot or inbox place: signalling NaNs, which arithmetic
+// does not return
+constexpr uint32_t kPersistEmpty32 = 0xffa5a5a5u;
+constexpr unsigned long long kPersistEmpty = 0xfff4dead4d415a45ull;
+constexpr int kErrAborted = 2;         // Scalars::err: a resident solve gave up waiting
+struct PersistGeom {
+  int N = 0;
+  int ncx = 0, ncy = 0;
+  int nwg = 0;   // ncx * ncy; 0: the grid has no resident form
+  int cls = 0;   // template class (points per thread)
+  int mx = 0, my = 0;  // most rows of a brick in x and in y
+  float cost_us = 0;   // estimate of an iteration alone
+};
 
 // Multigrid hierarchy of a session (preconditioner of the PLCG solve).
 // Level 0 is the fine grid: its right-hand side is the CG residual and its
@@ -184,6 +209,8 @@ struct DeviceState {
   // residual history of the current CG solve (written by the sweeps)
   double* hist = nullptr;
   int hist_cap = 0;
+  // resident solves: exchange slots, then the workgroups' inboxes
+  char* res = nullptr;
   // multigrid preconditioner (levels == 0: Jacobi)
   MgHierarchy mg;
   // force estimator: 0 equation "F_nostra", 1 equation "F_Benoit"
@@ -242,6 +269,7 @@ struct SweepArgs {
   int par_flip;    // batched launches: this session's parity is the launch's
                    // parity XOR par_flip (sessions that joined at different
                    // iterations share one launch)
+  void* res;       // resident solves: DeviceState::res
 };
 
 template <typename T>
@@ -306,6 +334,24 @@ SweepGeom make_sstep_geom(int N, int ppt, int cx, int nt);
 SweepGeom make_sstep_zv_geom(int N, int cx, int wv);
 // Threads per workgroup of a two-iteration shape.
 int sstep_threads(const SweepGeom& g);
+// Resident solve: every iteration of a solve in one launch. The geometry of
+// a grid (nwg = 0 where it has none), its dynamic LDS, how many of its
+// workgroups the device holds at once (cus: its CU count), and the launches:
+// one session, or the sessions of one class (device arrays as the batched
+// sweep's; no more workgroups than are resident together). spin: polls after
+// which a workgroup gives up waiting for the others.
+PersistGeom make_persist_geom(int N, bool fp32);
+size_t persist_bytes(const PersistGeom& g, bool fp32);  // of DeviceState::res
+hipError_t launch_persist_empty(const DeviceState& d, const PersistGeom& g, bool fp32,
+                                hipStream_t st);  // once, before the first solve
+size_t persist_lds_bytes(const PersistGeom& g, bool fp32);
+bool persist_batched(const PersistGeom& g);  // whether the batched launch has its class
+int persist_resident(const PersistGeom& g, bool fp32, bool batch, int cus);
+hipError_t launch_persist(const DeviceState& d, const PersistGeom& g, void* x, bool fp32,
+                          bool zero_x, int nprev_first, unsigned spin, hipStream_t st);
+hipError_t launch_persist_batch(const void* args_dev, const PersistGeom* geoms, const int* wg_begin,
+                                int count, int nwg, int cls, size_t lds, bool fp32, unsigned spin,
+                                hipStream_t st);
 // Fills x (G elements) with a fixed finite pattern.
 hipError_t launch_fill_pattern(void* x, long long G, bool fp32, hipStream_t st);
 // Batch helpers: {done, iters, err} of every session into out[3 * count];
