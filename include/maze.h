@@ -162,14 +162,14 @@ size_t maze_device_bytes(const maze_config* cfg);
 int maze_init(const maze_config* cfg, const double* charges_dev,
               const double* pos0_dev, maze_session** out, maze_stats* st);
 
-/* Resident solves. On grids up to 128^3 the one-iteration Jacobi PLCG runs
- * all iterations of a solve in one launch whose workgroups keep x, r, p and
- * A p on the chip and exchange boundary rows and sums (same per-point
- * arithmetic as the launched sweeps; the sums' order, so the last bits,
- * differ). maze_step, maze_solve, maze_step_batch and maze_batch_* all use it,
+/* Resident solves. On grids up to 128^3 the Jacobi PLCG (with or without
+ * MAZE_FLAG_SSTEP) runs all iterations of a solve in one launch whose
+ * workgroups keep x, r, p and A p on the chip and exchange boundary rows and
+ * sums (same per-point arithmetic as the launched sweeps; the sums' order,
+ * so the last bits, differ). maze_step, maze_solve, maze_step_batch and maze_batch_* all use it,
  * so a session's results stay bitwise those it gets alone; a batch above the
  * fill level (maze_step_batch) runs by launched sweeps where that is faster.
- * Sessions with a forced MAZE_SWEEP_SHAPE, timed ones (maze_profile_enable)
+ * Sessions with a forced launch shape, timed ones (maze_profile_enable)
  * and those created with MAZE_PERSIST=0 in the environment use launched
  * sweeps. Waits are bounded: a solve that other work keeps from running as
  * a whole for seconds is repeated by launched sweeps, as are the session's

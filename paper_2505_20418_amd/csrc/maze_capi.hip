@@ -201,12 +201,15 @@ static int part_stride_for(const DeviceState& d, const MarchGeom& g, const Sweep
   return m;
 }
 
-// Resident form of a session's solves: the one-iteration Jacobi PLCG on grids
-// whose vectors fit on the chip. MAZE_PERSIST=0 in the environment keeps to
-// launched sweeps.
+// Resident form of a session's solves: the Jacobi PLCG on grids whose vectors
+// fit on the chip, with or without MAZE_FLAG_SSTEP (the iterates are the same
+// in exact arithmetic, and a resident iteration moves no vectors that the
+// two-iteration form could spare: 128^3 FP64 MD step 5.20 ms launched in that
+// form, 2.6 resident). MAZE_PERSIST=0 in the environment keeps to launched
+// kernels.
 static PersistGeom persist_geom_of(const maze_config* c, int N) {
   const char* e = std::getenv("MAZE_PERSIST");
-  if ((e && e[0] == '0') || (c->flags & (MAZE_FLAG_MULTIGRID | MAZE_FLAG_SSTEP))) return {};
+  if ((e && e[0] == '0') || (c->flags & MAZE_FLAG_MULTIGRID)) return {};
   return make_persist_geom(N, c->precision == MAZE_MIXED);
 }
 
@@ -811,7 +814,7 @@ static bool persist_pays(const std::vector<const maze_session*>& ss) {
     (mixed ? f32 : f64) = true;
     nmax = std::max(nmax, s->d.N);
     res += (double)s->d.N * s->pgeom.cost_us;
-    bytes += (double)s->d.N * (double)s->d.G * (mixed ? 24.0 : 48.0);
+    bytes += (double)s->d.N * (double)s->d.G * (mixed ? 1.0 : 2.0) * (sstep_of(s) ? 16.0 : 24.0);
   }
   return res <= bytes / 5.0e6 + 12.0 * nmax * (1 + (f32 ? 1 : 0) + (f64 ? 1 : 0));
 }
@@ -2619,8 +2622,10 @@ int maze_init(const maze_config* cfg, const double* charges_dev, const double* p
   // launch shape of the CG sweep (timed on the still-unused buffers), then
   // clear them again for the first solve
   s->sweep = autotune_sweep(s);
-  SweepGeom forced;
-  if (forced_shape(d, mixed, &forced)) s->pgeom.nwg = 0;  // a forced shape is a launched sweep's
+  SweepGeom forced;  // a forced shape is a launched kernel's
+  if (forced_shape(d, mixed, &forced) ||
+      (sstep_of(s) && (forced_basis(d, mixed, &forced) || forced_update(d, mixed, &forced))))
+    s->pgeom.nwg = 0;
   if (s->pgeom.nwg > 0) {
     const int cus = device_cus();
     const bool batched = persist_batched(s->pgeom);
