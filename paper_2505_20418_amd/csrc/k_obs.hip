@@ -2,13 +2,14 @@
 // Langevin noise as an entry point of its own.
 //
 // * maze_langevin_noise: the normal deviates one OVRVO half step draws.
-// * maze_rdf_accumulate: pair-distance histograms for g_IJ(r). Tiles of
-//   256 x 256 ion pairs; each workgroup histograms its tile in LDS (integer
-//   atomics, so counts are exact and order-free) and adds the tile's counts
-//   to the global histogram.
+// * maze_rdf_accumulate: pair-distance histograms for g_IJ(r), over cells or
+//   over all pairs; each workgroup histograms in LDS (integer atomics, so
+//   counts are exact and order-free) and adds its counts to the global
+//   histogram.
 // * maze_tcf_*: velocity autocorrelation and mean squared displacement per
 //   species over a ring of time origins; one workgroup per live origin and
 //   sample, reduced in a fixed order.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -36,64 +37,331 @@ __global__ __launch_bounds__(kThreads) void k_langevin_noise(uint64_t seed, long
 
 // Squared minimum-image distance, rounded as written: each product and sum
 // on its own, no fused multiply-add (the bin of a pair is decided on it).
-__device__ __forceinline__ double min_image_r2(const double* a, const double* b, double box) {
+// The image number rint(dx / box) is taken from dx times 1 / box, which
+// rounds to the same integer unless it falls within rounding of a half; only
+// then is the division made. (A division per axis was most of a pair's work.)
+struct RdfBox {
+  double box, inv;
+};
+__device__ __forceinline__ double min_image_r2(double dx, double dy, double dz, const RdfBox& B) {
 #pragma clang fp contract(off)
-  double r2 = 0.0;
-#pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    double dx = b[d] - a[d];
-    dx = dx - box * rint(dx / box);
-    r2 = (d == 0) ? dx * dx : r2 + dx * dx;
+  const double tx = dx * B.inv, ty = dy * B.inv, tz = dz * B.inv;
+  double qx = rint(tx), qy = rint(ty), qz = rint(tz);
+  const double half = fmax(fmax(fabs(tx - qx), fabs(ty - qy)), fabs(tz - qz));
+  const double most = fmax(fmax(fabs(tx), fabs(ty)), fabs(tz));
+  if (!(half <= 0.499999) || !(most < 1e8)) {
+    qx = rint(dx / B.box);
+    qy = rint(dy / B.box);
+    qz = rint(dz / B.box);
   }
-  return r2;
+  dx = dx - B.box * qx;
+  dy = dy - B.box * qy;
+  dz = dz - B.box * qz;
+  return (dx * dx + dy * dy) + dz * dz;
 }
 
-// Tile (bi, bj), bj >= bi, of 256 x 256 ion pairs. LDS: the squared edges,
-// the tile's histogram (3 rows of nbins counters) and the j ions.
-__global__ __launch_bounds__(kThreads) void k_rdf_tile(const double* __restrict__ pos,
-                                                       const int32_t* __restrict__ species, int n,
-                                                       double box, const double* __restrict__ edges2,
-                                                       int nbins, unsigned long long* hist) {
-  const int bi = blockIdx.x, bj = blockIdx.y;
-  if (bj < bi) return;
-  extern __shared__ __align__(16) unsigned char smem[];
-  double* E = reinterpret_cast<double*>(smem);                 // nbins + 1
-  double* pj = E + (nbins + 1);                                // 3 * kThreads
-  int* sj = reinterpret_cast<int*>(pj + 3 * kThreads);         // kThreads
-  unsigned* H = reinterpret_cast<unsigned*>(sj + kThreads);    // 3 * nbins
-  const int tid = threadIdx.x;
-  for (int b = tid; b <= nbins; b += kThreads) E[b] = edges2[b];
-  for (int b = tid; b < 3 * nbins; b += kThreads) H[b] = 0u;
-  const int j0 = bj * kThreads, j = j0 + tid;
-  if (j < n) {
-    pj[3 * tid] = pos[3 * j];
-    pj[3 * tid + 1] = pos[3 * j + 1];
-    pj[3 * tid + 2] = pos[3 * j + 2];
-    sj[tid] = species[j] ? 1 : 0;  // any nonzero value counts as Cl
+// An ion for the pair search: its coordinates in units of 2^-32 of the box,
+// whose differences wrap to the nearest image by themselves, and 4 * index +
+// 2 * far + species.
+struct RdfIon {
+  uint32_t x, y, z;
+  int n;
+};
+// far: not finite or over 1e6 boxes away, where 2^-32 is not resolved.
+__device__ __forceinline__ uint32_t reduced(double v, double inv, bool& far) {
+  const double f = v * inv;
+  far = far || !(fabs(f) <= 1e6);
+  return (uint32_t)((f - floor(f)) * 4294967296.0);  // saturates at 2^32 - 1
+}
+
+// LDS of a workgroup of the pair histogram: the squared edges, its counters
+// (3 rows of nbins), the ions taken as i and as j, and per wavefront the
+// pairs whose exact distance is still to be formed.
+constexpr int kRdfThreads = 1024, kRdfWaves = kRdfThreads / 64;
+constexpr int kRdfI = 256, kRdfJ = 2 * kRdfThreads, kRdfQueue = 128;
+struct RdfLds {
+  RdfIon *I, *J;
+  double* E;
+  unsigned* H;
+  int *queue, *word;
+  __device__ RdfLds(unsigned char* smem, int nbins) {
+    I = reinterpret_cast<RdfIon*>(smem);
+    J = I + kRdfI;
+    E = reinterpret_cast<double*>(J + kRdfJ);
+    H = reinterpret_cast<unsigned*>(E + (nbins + 1));
+    queue = reinterpret_cast<int*>(H + 3 * nbins);
+    word = queue + kRdfWaves * kRdfQueue;
   }
-  __syncthreads();
-  const int i = bi * kThreads + tid;
-  if (i < n) {
-    const double pi[3] = {pos[3 * i], pos[3 * i + 1], pos[3 * i + 2]};
-    const int si = species[i] ? 1 : 0;
-    const int jn = min(kThreads, n - j0);
-    const double lo_e = E[0], hi_e = E[nbins];
-    for (int t = 0; t < jn; ++t) {
-      if (j0 + t <= i) continue;  // each pair once, i < j
-      const double r2 = min_image_r2(pi, pj + 3 * t, box);
-      if (!(r2 >= lo_e) || !(r2 < hi_e)) continue;
-      int lo = 0, hi = nbins;  // E[lo] <= r2 < E[hi]
-      while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (E[mid] <= r2) lo = mid;
-        else hi = mid;
+};
+size_t rdf_lds_bytes(int nbins) {
+  return sizeof(RdfIon) * (kRdfI + kRdfJ) + sizeof(double) * ((size_t)nbins + 1) +
+         sizeof(unsigned) * 3 * (size_t)nbins +
+         sizeof(int) * kRdfWaves * (kRdfQueue + 1);
+}
+
+// Counts a pair at squared distance r2 in row `row`: the bin with E[b] <= r2
+// < E[b + 1]. The search starts where bins of equal width in r would have it
+// (r0, per: their origin and number per length) and walks a few bins, then
+// bisects; any ascending edges give the same bin.
+__device__ __forceinline__ void count_pair(const RdfLds& s, int nbins, float r0, float per, double r2,
+                                           int row) {
+  int b = (int)((sqrtf((float)r2) - r0) * per);
+  b = min(max(b, 0), nbins - 1);
+  int steps = 0;
+  for (; steps < 4 && s.E[b] > r2; ++steps) --b;      // E[0] <= r2
+  for (; steps < 4 && !(r2 < s.E[b + 1]); ++steps) ++b;  // r2 < E[nbins]
+  if (s.E[b] > r2 || !(r2 < s.E[b + 1])) {
+    int lo = 0, hi = nbins;
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (s.E[mid] <= r2) lo = mid;
+      else hi = mid;
+    }
+    b = lo;
+  }
+  atomicAdd(&s.H[row * nbins + b], 1u);
+}
+
+// What the pair search needs besides its LDS.
+struct RdfJob {
+  const double* pos;
+  RdfBox B;
+  int nbins;
+  float r0, per;
+  double lo_e, hi_e;
+  bool any_far;  // whether there are far ions: their pairs are all left in
+  float far2;  // squared distance in 2^-32 boxes past which a pair is out of range
+};
+
+// The exact distance and bin of `n` queued pairs, one per lane.
+__device__ __forceinline__ void count_queue(const RdfLds& s, const RdfJob& q, const int* queue,
+                                            int n) {
+  const int lane = threadIdx.x & 63;
+  if (lane < n) {
+    const int pair = queue[lane];
+    const int a = s.I[pair & 255].n, b = s.J[pair >> 8].n;
+    const double* pa = q.pos + 3 * (size_t)(a >> 2);
+    const double* pb = q.pos + 3 * (size_t)(b >> 2);
+    const double r2 = min_image_r2(pb[0] - pa[0], pb[1] - pa[1], pb[2] - pa[2], q.B);
+    if (r2 >= q.lo_e && r2 < q.hi_e) count_pair(s, q.nbins, q.r0, q.per, r2, (a & 1) + (b & 1));
+  }
+}
+
+// Pairs of the i ions [0, ni) in LDS with the j ions [0, nj), each unordered
+// pair once (`flip`: where i's index is the larger, else where j's is). A
+// distance of 24 bits leaves out the pairs that are surely out of range; the rest
+// of a wavefront's pairs queue up until there are 64 of them, so the exact
+// distances and bins are formed by full wavefronts.
+__device__ __forceinline__ void count_block(const RdfLds& s, const RdfJob& q, bool flip, int ni,
+                                            int nj) {
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int* queue = s.queue + w * kRdfQueue;
+  int have = 0;
+  // a wavefront takes 64 j ions at a time; where these are fewer than the
+  // wavefronts, each takes a share of the i ions
+  const int jw = (nj + 63) / 64, split = max(1, kRdfWaves / jw);
+  if (w >= jw * split) return;
+  const int i0 = ni * (w / jw) / split, i1 = ni * (w / jw + 1) / split;
+  for (int j0 = (w % jw) * 64; j0 < nj; j0 += (split > 1 ? nj : kRdfThreads)) {
+    const int j = j0 + lane;
+    const RdfIon b = s.J[min(j, nj - 1)];
+    for (int i = split > 1 ? i0 : 0; i < (split > 1 ? i1 : ni); ++i) {
+      const RdfIon a = s.I[i];
+      const float dx = (float)(int)(b.x - a.x), dy = (float)(int)(b.y - a.y),
+                  dz = (float)(int)(b.z - a.z);
+      const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+      const bool once = flip ? (b.n >> 2) < (a.n >> 2) : (b.n >> 2) > (a.n >> 2);
+      bool maybe = !(d2 > q.far2);
+      if (q.any_far) maybe = maybe || ((a.n | b.n) & 2) != 0;
+      const unsigned long long m = __ballot(j < nj && once && maybe);
+      if (m == 0) continue;
+      if ((m >> lane) & 1ull) queue[have + __popcll(m & ((1ull << lane) - 1ull))] = j << 8 | i;
+      have += __popcll(m);
+      __builtin_amdgcn_wave_barrier();
+      if (have >= 64) {
+        have -= 64;
+        count_queue(s, q, queue + have, 64);
+        __builtin_amdgcn_wave_barrier();
       }
-      atomicAdd(&H[(si + sj[t]) * nbins + lo], 1u);
     }
   }
+  if (have > 0) count_queue(s, q, queue, have);
+}
+
+// Pair histograms. Where the largest distance counted is at most a sixth of
+// the box and the ions are many, the box is cut into nc^3 cells no shorter
+// than it: a workgroup takes cells in turn, gathers a cell's ions and those
+// of the 27 cells around it by scanning the positions (which stay in the
+// caches), and counts only pairs of these. Else, or if a position is not
+// finite or more than 1e6 boxes away (its cell would be uncertain), all
+// pairs, in blocks. The decision rests on the edges and the positions alone,
+// so every workgroup takes the same one. Counts are integers: exact in any
+// order.
+// What bounds it: FP64 work. With all pairs tested in FP64 and a division per
+// axis, 32768 ions to 12 of 102 A took 1.26 ms (4.3e11 pairs/s), though 0.7%
+// of these pairs are in range. The 24-bit test of all pairs takes 0.54 ms; the
+// cells (512 here) leave 5% of them and two scans of the positions per cell:
+// 0.26 ms. At 13824 ions and 216 cells the scans cost more than they save
+// (0.120 against 0.095 ms), so cells start at 16384 ions. 1728 ions: 203 us
+// before, 14 now.
+constexpr int kRdfCellsMin = 6, kRdfCellsMax = 16, kRdfIonsMin = 16384, kRdfBlockJ = 64;
+// Long side of a block of all pairs: many blocks for few ions, full workgroups
+// for many.
+__host__ __device__ inline int rdf_long(int n) { return n >= 4096 ? kRdfThreads : 256; }
+// Two kernels, since together they need more than the 64 registers that let
+// two workgroups of 16 wavefronts share a CU (with 91, one to a CU, all pairs
+// of 32768 ions took 0.80 ms): of both launches, the one whose form the edges
+// and positions ask for counts.
+template <bool CELLS>
+__global__ __launch_bounds__(kRdfThreads, 8) void k_rdf(const double* __restrict__ pos,
+                                                  const int32_t* __restrict__ species, int n,
+                                                  double box, const double* __restrict__ edges2,
+                                                  int nbins, unsigned long long* hist) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const RdfLds s(smem, nbins);
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  for (int b = tid; b <= nbins; b += kRdfThreads) s.E[b] = edges2[b];
+  for (int b = tid; b < 3 * nbins; b += kRdfThreads) s.H[b] = 0u;
   __syncthreads();
-  for (int b = tid; b < 3 * nbins; b += kThreads)
-    if (H[b] != 0u) atomicAdd(&hist[b], (unsigned long long)H[b]);
+  RdfJob q;
+  q.pos = pos;
+  q.B = RdfBox{box, 1.0 / box};
+  q.nbins = nbins;
+  q.any_far = false;
+  q.lo_e = s.E[0];
+  q.hi_e = s.E[nbins];
+  q.r0 = sqrtf(fmaxf((float)q.lo_e, 0.f));
+  q.per = (float)nbins / fmaxf(sqrtf((float)q.hi_e) - q.r0, 1e-30f);
+  // reduced coordinates are off by under 1e-9 boxes, squared distances by under
+  // 1e-5 of themselves plus 1e-8 boxes^2
+  q.far2 = (float)((q.hi_e / (box * box) * 1.00001 + 1e-8) * 18446744073709551616.0);
+  // cells per side: at least 2e-5 longer than the largest distance, which
+  // covers the rounding of the coordinates that cells are taken from
+  const double fc = floor(box / (sqrt(q.hi_e) * (1.0 + 2e-5)));
+  const int nc =
+      (n >= kRdfIonsMin && fc >= kRdfCellsMin) ? (int)fmin(fc, (double)kRdfCellsMax) : 0;
+  auto flush = [&]() {
+    __syncthreads();
+    for (int b = tid; b < 3 * nbins; b += kRdfThreads)
+      if (s.H[b] != 0u) {
+        atomicAdd(&hist[b], (unsigned long long)s.H[b]);
+        s.H[b] = 0u;
+      }
+    __syncthreads();
+  };
+  bool far = false;
+  auto ion_at = [&](int i, double x, double y, double z) {
+    RdfIon a;
+    bool f = false;
+    a.x = reduced(x, q.B.inv, f);
+    a.y = reduced(y, q.B.inv, f);
+    a.z = reduced(z, q.B.inv, f);
+    a.n = 4 * i + (f ? 2 : 0);
+    far = far || f;
+    return a;
+  };
+  auto ion_of = [&](int i) {
+    return ion_at(i, pos[3 * (size_t)i], pos[3 * (size_t)i + 1], pos[3 * (size_t)i + 2]);
+  };
+  // positions of the scan's next ions, fetched while the last are looked at
+  double nx = 0, ny = 0, nz = 0;
+  auto fetch = [&](int base) {
+    const size_t i = 3 * (size_t)min(base + tid, n - 1);
+    nx = pos[i];
+    ny = pos[i + 1];
+    nz = pos[i + 2];
+  };
+  auto cell1 = [&](uint32_t u) { return (int)__umulhi(u, (uint32_t)nc); };
+  // Appends to L, in scan order, those of the ions [base, base + kRdfThreads)
+  // for which take(ion) holds; `have` are in it, and of the sequence only
+  // [from, from + cap) is kept. Returns the new length of the sequence.
+  auto append = [&](int base, int have, RdfIon* L, int from, int cap, auto take) {
+    const int i = base + tid;
+    if (base == 0) fetch(0);
+    RdfIon a = ion_at(i, nx, ny, nz);
+    if (base + kRdfThreads < n) fetch(base + kRdfThreads);
+    const unsigned long long m = __ballot(i < n && take(a));
+    if (lane == 0) s.word[w] = __popcll(m);
+    __syncthreads();
+    int before = 0, total = 0;
+#pragma unroll 4
+    for (int v = 0; v < kRdfWaves; ++v) {
+      const int k = __builtin_amdgcn_readfirstlane(s.word[v]);
+      before += (v < w) ? k : 0;
+      total += k;
+    }
+    const int p = have + before + __popcll(m & ((1ull << lane) - 1ull)) - from;
+    if (((m >> lane) & 1ull) && p >= 0 && p < cap) {
+      a.n += species[i] ? 1 : 0;  // any nonzero value counts as Cl
+      L[p] = a;
+    }
+    __syncthreads();
+    return have + total;
+  };
+  if constexpr (CELLS) {
+    for (int c = blockIdx.x; c < nc * nc * nc; c += gridDim.x) {
+      const int cx = c / (nc * nc), cy = (c / nc) % nc, cz = c % nc;
+      for (int from = 0;; from += kRdfI) {  // the cell's ions, kRdfI at a time
+        int ni = 0;
+        for (int base = 0; base < n; base += kRdfThreads)
+          ni = append(base, ni, s.I, from, kRdfI, [&](const RdfIon& a) {
+            return cell1(a.x) == cx && cell1(a.y) == cy && cell1(a.z) == cz;
+          });
+        // seen by every workgroup in its first scan: all pairs instead
+        if (__syncthreads_or(far ? 1 : 0)) return;
+        const int here = min(ni - from, kRdfI);
+        int nj = 0;
+        for (int base = 0; here > 0 && base < n; base += kRdfThreads) {
+          nj = append(base, nj, s.J, 0, kRdfJ, [&](const RdfIon& a) {
+            auto near = [&](uint32_t v, int cc) {
+              const int d = cell1(v) - cc;
+              return d == 0 || d == 1 || d == -1 || d == nc - 1 || d == 1 - nc;
+            };
+            return near(a.x, cx) && near(a.y, cy) && near(a.z, cz);
+          });
+          // fewer than kRdfThreads are left over, so the next step's fit
+          if (nj >= kRdfThreads || base + kRdfThreads >= n) {
+            count_block(s, q, false, here, nj);
+            nj = 0;
+            __syncthreads();
+          }
+        }
+        if (ni - from <= kRdfI) break;
+      }
+    }
+  } else {
+    if (nc > 0) {
+      for (int i = tid; i < n; i += kRdfThreads) (void)ion_of(i);
+      if (!__syncthreads_or(far ? 1 : 0)) return;
+    }
+    q.any_far = true;  // cheap beside all pairs
+    const int wide = rdf_long(n);
+    const long long nbi = (n + wide - 1) / wide, nbj = (n + kRdfBlockJ - 1) / kRdfBlockJ;
+    int done = 0;
+    for (long long b = blockIdx.x; b < nbi * nbj; b += gridDim.x) {
+      // the long side (`wide` ions from i0 on) takes the place of
+      // j, the short one that of i
+      const int i0 = (int)(b / nbj) * wide, j0 = (int)(b % nbj) * kRdfBlockJ;
+      const int ni = min(wide, n - i0), nj = min(kRdfBlockJ, n - j0);
+      if (j0 + nj <= i0) continue;  // the short side's ions are all below
+      __syncthreads();
+      if (tid < ni) {
+        s.J[tid] = ion_of(i0 + tid);
+        s.J[tid].n += species[i0 + tid] ? 1 : 0;
+      }
+      if (tid < nj) {
+        s.I[tid] = ion_of(j0 + tid);
+        s.I[tid].n += species[j0 + tid] ? 1 : 0;
+      }
+      __syncthreads();
+      count_block(s, q, true, nj, ni);
+      if (++done == 1 << 17) {  // before a 32-bit counter could run over
+        done = 0;
+        flush();
+      }
+    }
+  }
+  flush();
 }
 
 // One workgroup per origin slot: the slot holds origin q (sample q*every),
@@ -182,20 +450,28 @@ int maze_rdf_accumulate(const double* pos_dev, const int32_t* species_dev, int32
       !edges2_dev || !hist_dev || (n > 0 && (!pos_dev || !species_dev)))
     return MAZE_E_INVALID;
   if (n < 2) return MAZE_OK;
-  const int nb = (n + kThreads - 1) / kThreads;
-  const size_t lds = sizeof(double) * ((size_t)nbins + 1 + 3 * kThreads) +
-                     sizeof(int) * kThreads + sizeof(unsigned) * 3 * (size_t)nbins;
+  const int wide = rdf_long(n);
+  const long long blocks = (((long long)n + wide - 1) / wide) *
+                           (((long long)n + kRdfBlockJ - 1) / kRdfBlockJ);
+  const size_t lds = rdf_lds_bytes(nbins);
   if (lds > 64 * 1024) {
     static bool raised = false;
     if (!raised) {
-      OBS_TRY(hipFuncSetAttribute((const void*)k_rdf_tile,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 1024));
+      for (const void* f : {(const void*)k_rdf<true>, (const void*)k_rdf<false>})
+        OBS_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    160 * 1024 - 1024));
       raised = true;
     }
   }
-  hipLaunchKernelGGL(k_rdf_tile, dim3(nb, nb), dim3(kThreads), lds, (hipStream_t)stream, pos_dev,
-                     species_dev, (int)n, box, edges2_dev, (int)nbins,
-                     reinterpret_cast<unsigned long long*>(hist_dev));
+  const dim3 grid((unsigned)std::min(blocks, 1024LL));
+  unsigned long long* hist = reinterpret_cast<unsigned long long*>(hist_dev);
+  if (n >= kRdfIonsMin) {
+    hipLaunchKernelGGL(k_rdf<true>, grid, dim3(kRdfThreads), lds, (hipStream_t)stream, pos_dev,
+                       species_dev, (int)n, box, edges2_dev, (int)nbins, hist);
+    OBS_TRY(hipGetLastError());
+  }
+  hipLaunchKernelGGL(k_rdf<false>, grid, dim3(kRdfThreads), lds, (hipStream_t)stream, pos_dev,
+                     species_dev, (int)n, box, edges2_dev, (int)nbins, hist);
   OBS_TRY(hipGetLastError());
   return MAZE_OK;
 }

@@ -99,3 +99,43 @@ def test_time_correlations_match_oracle(obs):
     np.testing.assert_allclose(msd, rm, rtol=1e-11, atol=1e-18)
     tc.close()
     run.close()
+
+
+# (cells per side, far images, edges): all pairs and cells, with ions in other
+# images; one position 1e7 boxes away and one not a number (no cells then);
+# edges of unequal width with a lower bound; a range of a sixth of the box
+@pytest.mark.parametrize("n_cells,kind,r_frac", [(5, "images", 0.3), (13, "images", 0.12),
+                                                 (13, "far", 0.12), (13, "nan", 0.12),
+                                                 (13, "edges", 0.16), (13, "images", 0.166)])
+def test_pair_counts_by_cells_and_all_pairs(obs, n_cells, kind, r_frac):
+    """Equal to the counts of every pair's squared distance, formed as the
+    header states it (torch rounds each product and sum on its own)."""
+    s = inputs.molten_nacl(n_cells, seed=n_cells)
+    pos = s.pos.copy()
+    pos[::7] += s.box * np.array([1.0, -2.0, 3.0])
+    if kind == "far":
+        pos[5] += s.box * 1e7
+    if kind == "nan":
+        pos[11, 1] = np.nan
+    h = obs.PairHistogram(dev(s.species, torch.int32), s.box, r_frac * s.box, 150)
+    if kind == "edges":
+        h.edges = np.sort(np.random.default_rng(3).uniform(2.0, r_frac * s.box, 151))
+        h.edges2 = dev(h.edges ** 2)
+    print(f"case: pair counts by {kind}, n={s.n_ions}", flush=True)
+    p = dev(pos)
+    h.accumulate(p)
+    e = h.edges2
+    want = torch.zeros(3 * 150, dtype=torch.int64, device="cuda")
+    sp = dev(s.species, torch.int64)
+    idx = torch.arange(s.n_ions, device="cuda")
+    for a in range(0, s.n_ions, 512):
+        r2 = torch.zeros(min(512, s.n_ions - a), s.n_ions, dtype=torch.float64, device="cuda")
+        for d in range(3):
+            dx = p[None, :, d] - p[a:a + 512, d, None]
+            dx = dx - torch.round(dx / s.box) * s.box
+            r2 = r2 + dx * dx
+        ok = (idx[None, :] > idx[a:a + 512, None]) & (r2 >= e[0]) & (r2 < e[-1])
+        i, j = torch.nonzero(ok, as_tuple=True)
+        b = torch.searchsorted(e, r2[i, j], right=True) - 1
+        want += torch.bincount((sp[a + i] + sp[j]) * 150 + b, minlength=450)
+    assert torch.equal(h.hist, want)
