@@ -389,7 +389,8 @@ struct OpRhsPoisson {
 // ---------------------------------------------------------------------------
 // Multigrid-preconditioned CG, direction pass: p = z + beta p_old (beta = 0
 // on the first iteration) and <p, A p> with A = -M on the fly. z is the
-// V-cycle output (FP64 or FP32). Staged field: p.
+// V-cycle output (FP64 or FP32). Staged field: p. Grids of odd N (one level);
+// k_mg.hip has the passes of even ones.
 // ---------------------------------------------------------------------------
 template <typename ZT>
 struct OpMgDir {

@@ -192,8 +192,8 @@ static int device_cus() {
 }
 
 static int part_stride_for(const DeviceState& d, const MarchGeom& g, const SweepGeom& w) {
-  int m = std::max({g.nwg, w.nwg, update_blocks(d.G), d.ntiles, 1});
   const int N = g.N;
+  int m = std::max({g.nwg, w.nwg, update_blocks(d.G), d.ntiles, 1});
   // sized for the fixed list; CU-multiple candidates that would not fit are
   // skipped by the tuner
   for (bool f : {false, true})
@@ -234,8 +234,9 @@ static Layout layout_for(const maze_config* c, int N, int* ntx_out, int* ntiles_
   DeviceState tmp;
   tmp.G = G;
   tmp.ntiles = ntiles;
-  const int stride = part_stride_for(tmp, choose_geom(N), choose_sweep(N));
   const bool mg = (c->flags & MAZE_FLAG_MULTIGRID) != 0;
+  int stride = part_stride_for(tmp, choose_geom(N), choose_sweep(N));
+  if (mg) stride = std::max(stride, mg_partials(N));
   // the multigrid-preconditioned CG is FP64 outside the V-cycle; the mixed
   // mode runs its V-cycle in FP32
   const bool mixed = c->precision == MAZE_MIXED && !mg;
@@ -275,13 +276,10 @@ static Layout layout_for(const maze_config* c, int N, int* ntx_out, int* ntiles_
     const size_t es = (c->precision == MAZE_MIXED) ? sizeof(float) : sizeof(double);
     const bool f32 = es == sizeof(float);
     L.add(f32 ? es * (size_t)G : 0);  // 27 z (FP64 uses the second r buffer)
-    L.add(f32 ? es * (size_t)G : 0);  // 28 rounded level-0 right-hand side
-    L.add(es * (size_t)G);            // 29 level-0 residual
     for (int l = 1; l < levels; ++l) {
       const size_t gl = (size_t)Ns[l] * Ns[l] * Ns[l];
       L.add(es * gl);  // x_l
       L.add(es * gl);  // b_l
-      L.add(es * gl);  // r_l
     }
   }
   if (ntx_out) *ntx_out = ntx;
@@ -1186,14 +1184,17 @@ static int run_mgcg(maze_session* s, double* x, CgJob& job) {
   const long long guard = (long long)s->cfg.max_iter + 8;
   for (long long i = 0;; ++i) {
     HIP_TRY(launch_mg_vcycle(d, m, d.r, m.z, m.fp32, st));
-    HIP_TRY(launch_mg_dot(d, d.r, m.z, m.fp32, st));
-    HIP_TRY(launch_finalize(d, FIN_MG_RHO, mg_dot_blocks(d.G), 0.0, 0.0, 0.0, nullptr, 0, 0, st));
+    HIP_TRY(launch_finalize(d, FIN_MG_RHO, mg_rho_count(m), 0.0, 0.0, 0.0, nullptr, 0, 0, st));
     double* pnew = d.p + (size_t)(i & 1) * d.G;
     const double* pold = d.p + (size_t)((i & 1) ^ 1) * d.G;
-    HIP_TRY(launch_mg_dir(d, g, m.z, m.fp32, pold, pnew, st));
-    HIP_TRY(launch_finalize(d, FIN_MG_MU, g.nwg, 0.0, 0.0, 0.0, nullptr, 0, 0, st));
-    HIP_TRY(launch_mg_upd(d, g, pnew, x, st));
-    HIP_TRY(launch_finalize(d, FIN_MG_CONV, g.nwg, 0.0, 0.0, 0.0, nullptr, 0, 0, st));
+    const bool pairs = mg_dir_ok(d.N);
+    if (pairs) HIP_TRY(launch_mg_dir_pairs(d, m.z, m.fp32, pold, pnew, st));
+    else HIP_TRY(launch_mg_dir(d, g, m.z, m.fp32, pold, pnew, st));
+    const int np = pairs ? mg_dir_count(d.N) : g.nwg;
+    HIP_TRY(launch_finalize(d, FIN_MG_MU, np, 0.0, 0.0, 0.0, nullptr, 0, 0, st));
+    if (pairs) HIP_TRY(launch_mg_upd_pairs(d, pnew, x, st));
+    else HIP_TRY(launch_mg_upd(d, g, pnew, x, st));
+    HIP_TRY(launch_finalize(d, FIN_MG_CONV, np, 0.0, 0.0, 0.0, nullptr, 0, 0, st));
     const int slot = (int)(i & 1);
     HIP_TRY(hipMemcpyAsync(&s->host_sc[slot], d.sc, sizeof(Scalars), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipEventRecord(s->ev[slot], st));
@@ -2597,12 +2598,9 @@ int maze_init(const maze_config* cfg, const double* charges_dev, const double* p
       m.c[l] = std::pow(0.25, l);
     }
     m.z = m.fp32 ? at(27) : (void*)(d.r + d.G);
-    m.b[0] = m.fp32 ? at(28) : nullptr;
-    m.r[0] = at(29);
     for (int l = 1; l < m.levels; ++l) {
-      m.x[l] = at(30 + 3 * (l - 1));
-      m.b[l] = at(31 + 3 * (l - 1));
-      m.r[l] = at(32 + 3 * (l - 1));
+      m.x[l] = at(28 + 2 * (l - 1));
+      m.b[l] = at(29 + 2 * (l - 1));
     }
   }
   if (hipHostMalloc((void**)&s->host_sc, 2 * sizeof(Scalars), hipHostMallocDefault) !=

@@ -145,9 +145,8 @@ struct PersistGeom {
 
 // Multigrid hierarchy of a session (preconditioner of the PLCG solve).
 // Level 0 is the fine grid: its right-hand side is the CG residual and its
-// solution the preconditioned residual z; x / b / r of levels >= 1, the
-// level-0 residual temporary r[0] and, for an FP32 preconditioner, the
-// rounded right-hand side b[0] live in the session allocation.
+// solution the preconditioned residual z; x / b of levels >= 1 live in the
+// session allocation.
 constexpr int kMgMaxLevels = 12;
 struct MgHierarchy {
   int levels = 0;
@@ -157,7 +156,6 @@ struct MgHierarchy {
   double c[kMgMaxLevels] = {0};   // operator scale 4^-l
   void* x[kMgMaxLevels] = {nullptr};
   void* b[kMgMaxLevels] = {nullptr};
-  void* r[kMgMaxLevels] = {nullptr};
   void* z = nullptr;              // preconditioned residual (T)
 };
 
@@ -359,14 +357,21 @@ hipError_t launch_fill_pattern(void* x, long long G, bool fp32, hipStream_t st);
 hipError_t launch_batch_poll(Scalars* const* scs, int count, int32_t* out, hipStream_t st);
 hipError_t launch_batch_scalars(Scalars* const* scs, int count, Scalars* out, hipStream_t st);
 
-// Multigrid-preconditioned CG: z = V-cycle(r) (fp32: FP32 hierarchy); the
-// partials of <r, z>; the direction pass p_new = z + beta p_old with
-// <p, A p>; the update pass x += alpha p, r -= alpha A p with ||r||.
+// Multigrid-preconditioned CG: z = V-cycle(r) (fp32: FP32 hierarchy) and the
+// mg_rho_count partials of <r, z> (at most mg_partials(N) on any hierarchy);
+// the direction pass p_new = z + beta p_old with <p, A p>; the update pass
+// x += alpha p, r -= alpha A p with ||r||.
 hipError_t launch_mg_vcycle(const DeviceState& d, const MgHierarchy& m, const double* r, void* z,
                             bool fp32, hipStream_t st);
-hipError_t launch_mg_dot(const DeviceState& d, const double* r, const void* z, bool fp32,
-                         hipStream_t st);
-int mg_dot_blocks(long long G);
+int mg_rho_count(const MgHierarchy& m);
+int mg_partials(int N);
+// The direction and update passes on grids of even N (mg_dir_ok),
+// mg_dir_count partials.
+bool mg_dir_ok(int N);
+int mg_dir_count(int N);
+hipError_t launch_mg_dir_pairs(const DeviceState& d, const void* z, bool fp32, const double* pold,
+                               double* pnew, hipStream_t st);
+hipError_t launch_mg_upd_pairs(const DeviceState& d, const double* p, double* x, hipStream_t st);
 int mg_plan(int N, int* Ns, int max_levels);
 hipError_t launch_mg_dir(const DeviceState& d, const MarchGeom& g, const void* z, bool fp32,
                          const double* pold, double* pnew, hipStream_t st);

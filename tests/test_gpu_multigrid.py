@@ -107,3 +107,74 @@ def test_multigrid_256_iterations_and_residual(maze, precision):
     F_ref = oracle.gather(p, s.charges, s.box, phi)
     assert rel(out["forces"], F_ref) <= 1e-13
     g.close()
+
+
+def reference_iterations(b, thr):
+    """Iterations of the multigrid-preconditioned CG for A x = b (A = -M) from
+    zero, the V-cycle written out pass by pass in float64."""
+    def nbr(x):
+        return sum(torch.roll(x, s, a) for a in range(3) for s in (1, -1))
+
+    def half_sweep(x, b, c, color):
+        n = x.shape[0]
+        i = torch.arange(n, device=x.device)
+        par = (i[:, None, None] + i[None, :, None] + i[None, None, :]) % 2
+        return torch.where(par == color, (b / c + nbr(x)) / 6, x)
+
+    def vcycle(b, c):
+        n = b.shape[0]
+        if n % 2 or n // 2 < 4:  # exact, by the eigenvalues of the periodic stencil
+            lam = 2 - 2 * torch.cos(2 * np.pi * torch.arange(n, device=b.device, dtype=b.dtype) / n)
+            lam = c * (lam[:, None, None] + lam[None, :, None] + lam[None, None, :])
+            f = torch.fft.fftn(b - b.mean())
+            lam[0, 0, 0] = 1
+            f[0, 0, 0] = 0
+            return torch.fft.ifftn(f / lam).real
+        x = half_sweep(half_sweep(torch.zeros_like(b), b, c, 0), b, c, 1)
+        r = b - c * (6 * x - nbr(x))
+        for a in range(3):
+            r = r / 2 + (torch.roll(r, 1, a) + torch.roll(r, -1, a)) / 4
+        e = vcycle(r[::2, ::2, ::2].contiguous(), c / 4)
+        for a in range(3):
+            e = torch.stack([e, (e + torch.roll(e, -1, a)) / 2], a + 1).flatten(a, a + 1)
+        x = x + e
+        return half_sweep(half_sweep(x, b, c, 1), b, c, 0)
+
+    r, p, rho = b.clone(), None, None
+    for it in range(60):
+        if r.norm().item() <= thr:
+            return it
+        z = vcycle(r, 1.0)
+        new = (r * z).sum()
+        p = z if p is None else z + new / rho * p
+        rho = new
+        ap = 6 * p - nbr(p)
+        r = r - rho / (p * ap).sum() * ap
+    return 60
+
+
+# one workgroup alone (16, and 18 down to 9 by a workgroup's CG); tiles of four
+# rows with a remainder (20, 28, 44), of eight (96, 112), pieces of rows (144,
+# 160), long chunks (192)
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("N", [16, 18, 20, 28, 44, 96, 112, 144, 160, 192])
+def test_vcycle_by_its_iterations(maze, precision, N):
+    """The fused V-cycle is the one of the plain passes: the preconditioned CG
+    takes the iterations of the reference (one more or less, where the residual
+    of the last one is the tolerance up to the cycle's rounding)."""
+    rng = np.random.default_rng(N)
+    n, h, tol = 64, 0.5, 1e-8
+    pos = rng.uniform(0, N * h, (n, 3))
+    q = np.where(np.arange(n) % 2, 1.0, -1.0)
+    print(f"case: V-cycle N={N} precision={precision}", flush=True)
+    g = maze.Session(dev(q), dev(pos), N * h, h, tol=tol, precision=precision,
+                     flags=maze.MAZE_FLAG_MULTIGRID)
+    out = g.solve(dev(pos))
+    s = dev(-4 * np.pi / h * oracle.spread(pos, q, N * h, N))
+    s = s - s.mean()
+    want = reference_iterations(-s, tol * s.norm().item())
+    assert abs(out["stats"]["iters"] - want) <= 1, (out["stats"], want)
+    r = -s - (6 * out["field"] - sum(torch.roll(out["field"], k, a)
+                                     for a in range(3) for k in (1, -1)))
+    assert r.norm().item() <= 1.001 * tol * s.norm().item()
+    g.close()
