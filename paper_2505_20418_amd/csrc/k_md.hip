@@ -58,30 +58,136 @@ __device__ __forceinline__ double bmh_dvdr(const double* row, double r) {
   return -row[0] * row[1] * exp(row[1] * (row[2] - r)) + 6.0 * row[3] / r7 + 8.0 * row[4] / r9;
 }
 
-// Short range: one thread per ion i, all j streamed through LDS in tiles.
-// Minimum image, cutoff, energy shifted to zero at the cutoff. Each pair is
-// evaluated from both sides (force on i only), so no atomics are needed;
-// the energy counts each pair once (j > i).
+// Short range: one wavefront per ion i (four to a workgroup). Its lanes test
+// candidates j; the pairs within the cutoff queue up in LDS until there are
+// 64, so the pair terms (a root, divisions and exponentials in FP64, most of
+// the kernel's instructions) are formed by full wavefronts. Minimum image,
+// cutoff, energy shifted to zero at the cutoff. Each pair is evaluated from
+// both sides (force on i only), so no atomics are needed; the energy counts
+// each pair once (j > i). The terms are added in the order of the candidates,
+// one sum per component and class of candidates, so the result does not
+// depend on how the pairs fell into wavefronts.
+// Bound by latency on small systems (tiles -> ions -> positions): 7 us for 216
+// ions in all pairs, 8 for 512 by tiles, 71 for 32768 (one thread an ion in all
+// pairs 34, eight lanes an ion 42 and 78: the lanes took a pair term whenever
+// one of them had a pair).
+constexpr int kBmhWaves = kThreads / 64;
+constexpr int kBmhClasses = 8;
+
+struct BmhLds {
+  int queue[128];
+  uint8_t cls[128];
+  double f[64], d[3][64], e[64];
+};
+
+struct BmhWave {
+  const MdParams& p;
+  const double* pos;
+  const int32_t* species;
+  const double* tab;  // LDS: the 15 coefficients, then the 3 energy shifts
+  BmhLds& s;
+  int i, si, have;    // the same in every lane
+  double xi, yi, zi;
+  double acc;         // lane 4 c + k: component k (3: energy) of class c
+
+  __device__ __forceinline__ double separation(double xj, double yj, double zj, double d[3]) const {
+    double dx = xi - xj, dy = yi - yj, dz = zi - zj;
+    dx -= p.box * rint(dx * p.inv_box);
+    dy -= p.box * rint(dy * p.inv_box);
+    dz -= p.box * rint(dz * p.inv_box);
+    d[0] = dx;
+    d[1] = dy;
+    d[2] = dz;
+    return dx * dx + dy * dy + dz * dz;
+  }
+  // Candidate j of a class at (x, y, z), if `on`; every lane calls. Classes
+  // do not decrease from lane to lane and call to call.
+  __device__ __forceinline__ void test(bool on, int j, int cls, double x, double y, double z) {
+    double d[3];
+    const double r2 = separation(x, y, z, d);
+    const bool in = on && j != i && !(r2 >= p.cutoff * p.cutoff);
+    const unsigned long long m = __ballot(in);
+    const int lane = threadIdx.x & 63;
+    if (in) {
+      const int at = have + __popcll(m & ((1ull << lane) - 1));
+      s.queue[at] = j;
+      s.cls[at] = (uint8_t)cls;
+    }
+    have += __popcll(m);
+    if (have >= 64) {
+      drain(64);
+      have -= 64;
+      const int rest = lane < have ? s.queue[64 + lane] : 0;
+      const int rc = lane < have ? s.cls[64 + lane] : 0;
+      __threadfence_block();
+      if (lane < have) {
+        s.queue[lane] = rest;
+        s.cls[lane] = (uint8_t)rc;
+      }
+    }
+  }
+  // Adds the pairs with the first n of the queue.
+  __device__ __forceinline__ void drain(int n) {
+    const int lane = threadIdx.x & 63;
+    __threadfence_block();
+    const int cls = lane < n ? s.cls[lane] : kBmhClasses;
+    if (lane < n) {
+      const int j = s.queue[lane];
+      double d[3];
+      const double r = sqrt(separation(pos[3 * j], pos[3 * j + 1], pos[3 * j + 2], d));
+      const int t = si + species[j];
+      const double* row = tab + 5 * t;
+      s.f[lane] = -bmh_dvdr(row, r) / r;
+      s.d[0][lane] = d[0];
+      s.d[1][lane] = d[1];
+      s.d[2][lane] = d[2];
+      s.e[lane] = j > i ? bmh_v(row, r) - tab[15 + t] : 0.0;
+    }
+    __threadfence_block();
+    // the queue is in order of class: a class's pairs are one run of it
+    int b = 0, en = 0;
+#pragma unroll
+    for (int c = 0; c < kBmhClasses; ++c) {
+      const int before = __popcll(__ballot(cls < c)), upto = __popcll(__ballot(cls <= c));
+      if (lane >> 2 == c) {
+        b = before;
+        en = upto;
+      }
+    }
+    const int k = lane & 3;
+    for (int q = b; q < en; ++q) acc = k < 3 ? fma(s.f[q], s.d[k][q], acc) : acc + s.e[q];
+    __threadfence_block();
+  }
+  // Ends the ion: its force; its energy is lane 3's.
+  __device__ __forceinline__ double finish(double* f_sr) {
+    drain(have);
+#pragma unroll
+    for (int m = 2 * kBmhClasses; m >= 4; m >>= 1) acc += __shfl_xor(acc, m, 64);
+    const int lane = threadIdx.x & 63;
+    if (lane < 3) f_sr[3 * i + lane] = acc;
+    return lane == 3 ? acc : 0.0;
+  }
+};
+
+// The coefficients and the shifts into LDS; the caller waits.
+__device__ __forceinline__ void bmh_table(const MdParams& p, double* tab) {
+  const int t = threadIdx.x;
+  if (t < 15) tab[t] = p.tab[t];
+  if (t < 3) tab[15 + t] = bmh_v(p.tab + 5 * t, p.cutoff);
+}
+
+// All pairs: every j, staged through LDS for the workgroup's four ions.
 __global__ __launch_bounds__(kThreads) void k_md_bmh(MdParams p, const double* __restrict__ pos,
                                                      const int32_t* __restrict__ species,
                                                      double* __restrict__ f_sr, double* part_e) {
-  __shared__ double sx[kThreads], sy[kThreads], sz[kThreads];
-  __shared__ int ss[kThreads];
-  __shared__ double red[8];
-  const int i = blockIdx.x * kThreads + threadIdx.x;
-  const bool act = i < p.n;
-  double xi = 0, yi = 0, zi = 0;
-  int si = 0;
-  if (act) {
-    xi = pos[3 * i];
-    yi = pos[3 * i + 1];
-    zi = pos[3 * i + 2];
-    si = species[i];
-  }
-  double vshift[3];
-  for (int t = 0; t < 3; ++t) vshift[t] = bmh_v(p.tab + 5 * t, p.cutoff);
-  const double rc2 = p.cutoff * p.cutoff;
-  double fx = 0, fy = 0, fz = 0, e = 0;
+  __shared__ double sx[kThreads], sy[kThreads], sz[kThreads], tab[18], red[8];
+  __shared__ BmhLds lds[kBmhWaves];
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int s = __builtin_amdgcn_readfirstlane(blockIdx.x * kBmhWaves + w);
+  const int i = min(s, p.n - 1);
+  bmh_table(p, tab);
+  BmhWave b{p, pos, species, tab, lds[w], i, species[i], 0, pos[3 * i], pos[3 * i + 1],
+            pos[3 * i + 2], 0.0};
   for (int base = 0; base < p.n; base += kThreads) {
     const int j = base + threadIdx.x;
     __syncthreads();
@@ -89,48 +195,26 @@ __global__ __launch_bounds__(kThreads) void k_md_bmh(MdParams p, const double* _
       sx[threadIdx.x] = pos[3 * j];
       sy[threadIdx.x] = pos[3 * j + 1];
       sz[threadIdx.x] = pos[3 * j + 2];
-      ss[threadIdx.x] = species[j];
     }
     __syncthreads();
     const int m = min(kThreads, p.n - base);
-    if (act) {
-      for (int k = 0; k < m; ++k) {
-        const int jj = base + k;
-        if (jj == i) continue;
-        double dx = xi - sx[k], dy = yi - sy[k], dz = zi - sz[k];
-        dx -= p.box * rint(dx * p.inv_box);
-        dy -= p.box * rint(dy * p.inv_box);
-        dz -= p.box * rint(dz * p.inv_box);
-        const double r2 = dx * dx + dy * dy + dz * dz;
-        if (r2 >= rc2) continue;
-        const double r = sqrt(r2);
-        const int t = si + ss[k];
-        const double* row = p.tab + 5 * t;
-        const double f = -bmh_dvdr(row, r) / r;
-        fx += f * dx;
-        fy += f * dy;
-        fz += f * dz;
-        if (jj > i) e += bmh_v(row, r) - vshift[t];
+    if (s < p.n)
+      for (int k0 = 0; k0 < m; k0 += 64) {
+        const int k = min(k0 + lane, m - 1);
+        b.test(k0 + lane < m, base + k, 0, sx[k], sy[k], sz[k]);
       }
-    }
   }
-  if (act) {
-    f_sr[3 * i] = fx;
-    f_sr[3 * i + 1] = fy;
-    f_sr[3 * i + 2] = fz;
-  }
+  const double e = s < p.n ? b.finish(f_sr) : 0.0;
   const double te = block_sum(e, red);
   if (threadIdx.x == 0) part_e[blockIdx.x] = te;
 }
 
-// Short range over the tiles of the MaZe binning (tiles of kTile^3 grid
-// points, filled by the assignment of the step at the same positions): each
-// ion visits the (2R+1)^3 tiles around its own, R tiles covering the cutoff.
-// Eight lanes share one ion, each taking every eighth tile of the block in a
-// fixed order, and the lanes' sums are combined by a fixed butterfly, so the
-// result is deterministic. Energy counts each pair once (j > i) and is
-// reduced per workgroup into e_part.
-constexpr int kBmhLanes = 8;
+// Over the tiles of the MaZe binning (tiles of kTile^3 grid points, filled by
+// the assignment of the step at the same positions): each ion visits the
+// (2R+1)^3 tiles around its own, R tiles covering the cutoff, in eight classes
+// (every eighth tile). A lane looks up a tile; the tiles' ions are listed in
+// LDS, kBmhList at a time, and tested 64 at a time.
+constexpr int kBmhList = 256;
 
 struct BmhTiles {
   const int32_t* tile_start;
@@ -145,62 +229,68 @@ __global__ __launch_bounds__(kThreads) void k_md_bmh_tiles(MdParams p, BmhTiles 
                                                            const int32_t* __restrict__ species,
                                                            double* __restrict__ f_sr,
                                                            double* e_part) {
-  __shared__ double red[8];
-  const int gt = blockIdx.x * kThreads + threadIdx.x;
-  const int s = gt / kBmhLanes, lane = gt % kBmhLanes;
-  const bool act = s < p.n;
-  double fx = 0, fy = 0, fz = 0, e = 0;
-  int i = 0;
-  if (act) {
-    i = t.sorted_idx[s];
-    const double xi = pos[3 * i], yi = pos[3 * i + 1], zi = pos[3 * i + 2];
-    const int si = species[i];
+  __shared__ double tab[18], red[8];
+  __shared__ BmhLds lds[kBmhWaves];
+  __shared__ int list[kBmhWaves][kBmhList];
+  __shared__ uint8_t list_cls[kBmhWaves][kBmhList];
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int s = __builtin_amdgcn_readfirstlane(blockIdx.x * kBmhWaves + w);
+  bmh_table(p, tab);
+  __syncthreads();
+  double e = 0.0;
+  if (s < p.n) {
+    const int i = t.sorted_idx[s];
     const int tx = t.s_cell[3 * s] / kTile, ty = t.s_cell[3 * s + 1] / kTile,
               tz = t.s_cell[3 * s + 2] / kTile;
-    double vshift[3];
-    for (int q = 0; q < 3; ++q) vshift[q] = bmh_v(p.tab + 5 * q, p.cutoff);
-    const double rc2 = p.cutoff * p.cutoff;
+    BmhWave b{p, pos, species, tab, lds[w], i, species[i], 0, pos[3 * i], pos[3 * i + 1],
+              pos[3 * i + 2], 0.0};
+    int* const l = list[w];
+    uint8_t* const lc = list_cls[w];
     const int W = 2 * t.R + 1, ntot = W * W * W;
-    for (int c = lane; c < ntot; c += kBmhLanes) {
-      int ax = tx + c / (W * W) - t.R, ay = ty + (c / W) % W - t.R, az = tz + c % W - t.R;
-      ax = (ax < 0) ? ax + t.ntx : (ax >= t.ntx ? ax - t.ntx : ax);
-      ay = (ay < 0) ? ay + t.ntx : (ay >= t.ntx ? ay - t.ntx : ay);
-      az = (az < 0) ? az + t.ntx : (az >= t.ntx ? az - t.ntx : az);
-      const int ct = (ax * t.ntx + ay) * t.ntx + az;
-      const int b = t.tile_start[ct], en = t.tile_start[ct + 1];
-      for (int s2 = b; s2 < en; ++s2) {
-        const int j = t.sorted_idx[s2];
-        if (j == i) continue;
-        double dx = xi - pos[3 * j], dy = yi - pos[3 * j + 1], dz = zi - pos[3 * j + 2];
-        dx -= p.box * rint(dx * p.inv_box);
-        dy -= p.box * rint(dy * p.inv_box);
-        dz -= p.box * rint(dz * p.inv_box);
-        const double r2 = dx * dx + dy * dy + dz * dz;
-        if (r2 >= rc2) continue;
-        const double r = sqrt(r2);
-        const int q = si + species[j];
-        const double* row = p.tab + 5 * q;
-        const double f = -bmh_dvdr(row, r) / r;
-        fx += f * dx;
-        fy += f * dy;
-        fz += f * dz;
-        if (j > i) e += bmh_v(row, r) - vshift[q];
+    // tile c belongs to class c mod 8; class by class, the first `rem` classes
+    // have per + 1 tiles
+    const int per = ntot / kBmhClasses, rem = ntot % kBmhClasses;
+    for (int c0 = 0; c0 < ntot; c0 += 64) {
+      const int u = c0 + lane, big = rem * (per + 1);
+      const int cls = u < big ? u / (per + 1) : rem + (u - big) / per;
+      const int c = cls + kBmhClasses * (u < big ? u % (per + 1) : (u - big) % per);
+      int first = 0, count = 0;
+      if (u < ntot) {
+        int ax = tx + c / (W * W) - t.R, ay = ty + (c / W) % W - t.R, az = tz + c % W - t.R;
+        ax = (ax < 0) ? ax + t.ntx : (ax >= t.ntx ? ax - t.ntx : ax);
+        ay = (ay < 0) ? ay + t.ntx : (ay >= t.ntx ? ay - t.ntx : ay);
+        az = (az < 0) ? az + t.ntx : (az >= t.ntx ? az - t.ntx : az);
+        const int ct = (ax * t.ntx + ay) * t.ntx + az;
+        first = t.tile_start[ct];
+        count = t.tile_start[ct + 1] - first;
+      }
+      // where this tile's ions begin in the list of the 64 tiles
+      int at = count;
+#pragma unroll
+      for (int m = 1; m < 64; m <<= 1) {
+        const int v = __shfl_up(at, m, 64);
+        if (lane >= m) at += v;
+      }
+      const int total = __shfl(at, 63, 64);
+      at -= count;
+      for (int l0 = 0; l0 < total; l0 += kBmhList) {
+        const int k1 = min(count, l0 + kBmhList - at);
+        for (int k = max(0, l0 - at); k < k1; ++k) {
+          l[at + k - l0] = first + k;
+          lc[at + k - l0] = (uint8_t)cls;
+        }
+        __threadfence_block();
+        const int m = min(kBmhList, total - l0);
+        for (int k = 0; k < m; k += 64) {
+          const int h = min(k + lane, m - 1), j = t.sorted_idx[l[h]];
+          b.test(k + lane < m, j, lc[h], pos[3 * j], pos[3 * j + 1], pos[3 * j + 2]);
+        }
+        __threadfence_block();
       }
     }
+    e = b.finish(f_sr);
   }
-#pragma unroll
-  for (int m = kBmhLanes / 2; m > 0; m >>= 1) {
-    fx += __shfl_xor(fx, m, 64);
-    fy += __shfl_xor(fy, m, 64);
-    fz += __shfl_xor(fz, m, 64);
-    e += __shfl_xor(e, m, 64);
-  }
-  if (act && lane == 0) {
-    f_sr[3 * i] = fx;
-    f_sr[3 * i + 1] = fy;
-    f_sr[3 * i + 2] = fz;
-  }
-  const double te = block_sum((lane == 0) ? e : 0.0, red);
+  const double te = block_sum(e, red);
   if (threadIdx.x == 0) e_part[blockIdx.x] = te;
 }
 
@@ -328,25 +418,19 @@ static int bmh_tile_radius(const DeviceState& d, double cutoff) {
   return (2 * R + 1 <= d.ntx) ? R : 0;
 }
 
-int md_energy_partials(const DeviceState& d, double cutoff) {
-  const int n = d.n_ions;
-  if (bmh_tile_radius(d, cutoff) > 0)
-    return (int)(((long long)n * kBmhLanes + kThreads - 1) / kThreads);
-  return md_blocks(n);
-}
+int md_energy_partials(int n_ions) { return (n_ions + kBmhWaves - 1) / kBmhWaves; }
 
 hipError_t launch_md_bmh(const maze_md_state& md, const DeviceState& d, hipStream_t st) {
   MdParams p = md_params(md, d.box);
-  const int n = md.n_ions;
   const int R = bmh_tile_radius(d, md.cutoff);
+  const dim3 grid(md_energy_partials(md.n_ions));
   if (R > 0) {
     BmhTiles t{d.tile_start, d.sorted_idx, d.s_cell, d.ntx, R};
-    hipLaunchKernelGGL(k_md_bmh_tiles, dim3(md_energy_partials(d, md.cutoff)), dim3(kThreads), 0,
-                       st, p, t, (const double*)md.pos_dev, md.species_dev, md.f_sr_dev,
-                       d.md_epart);
-  } else {
-    hipLaunchKernelGGL(k_md_bmh, dim3(md_blocks(n)), dim3(kThreads), 0, st, p,
+    hipLaunchKernelGGL(k_md_bmh_tiles, grid, dim3(kThreads), 0, st, p, t,
                        (const double*)md.pos_dev, md.species_dev, md.f_sr_dev, d.md_epart);
+  } else {
+    hipLaunchKernelGGL(k_md_bmh, grid, dim3(kThreads), 0, st, p, (const double*)md.pos_dev,
+                       md.species_dev, md.f_sr_dev, d.md_epart);
   }
   return hipGetLastError();
 }
@@ -361,7 +445,7 @@ static hipError_t md_finish(const maze_md_state& md, const DeviceState& d, int d
                      (const double*)md.f_sr_dev, (const double*)md.scratch_dev,
                      (const double*)(md.scratch_dev + 3 * (size_t)n), do_kick, part, nb);
   hipLaunchKernelGGL(k_md_finish, dim3(1), dim3(kThreads), 0, st, (const double*)part, nb,
-                     (const double*)d.md_epart, md_energy_partials(d, md.cutoff),
+                     (const double*)d.md_epart, md_energy_partials(md.n_ions),
                      do_kick ? 0 : 1, md.scalars_dev);
   return hipGetLastError();
 }

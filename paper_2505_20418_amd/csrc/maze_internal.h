@@ -406,7 +406,7 @@ hipError_t launch_md_bmh(const maze_md_state& md, const DeviceState& d, hipStrea
 hipError_t launch_md_finish(const maze_md_state& md, const DeviceState& d, long long step,
                             hipStream_t st);
 hipError_t launch_md_prime(const maze_md_state& md, const DeviceState& d, hipStream_t st);
-// Number of short-range energy partials for this cutoff (<= n_ions).
-int md_energy_partials(const DeviceState& d, double cutoff);
+// Number of short-range energy partials (<= n_ions).
+int md_energy_partials(int n_ions);
 
 }  // namespace maze

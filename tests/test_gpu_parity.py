@@ -324,3 +324,26 @@ def test_short_range_tiles_match_oracle(maze, n_cells, grid_n):
     assert np.abs(F - F_ref).max() <= 1e-10 * max(1.0, np.abs(F_ref).max())
     assert abs(run.observables()["v_sr"] - e_ref) <= 1e-10 * abs(e_ref)
     run.close()
+
+
+# a wavefront per ion: fewer ions than a workgroup holds, ions beyond one
+# staged block, more neighbours than one queue (318 at half the box), more ions
+# in 64 tiles than one list (5 a tile at 56^3), partial last tiles (60^3)
+@pytest.mark.parametrize("n,n_cells,scale,grid_n", [
+    (1, 2, 1.0, 32), (5, 2, 1.0, 32), (66, 4, 0.5, 32), (301, 4, 0.5, 32), (1728, 6, 0.5, 32),
+    (1728, 6, 0.5, 56), (1726, 6, 0.5, 128), (509, 4, 1.0, 60)])
+def test_short_range_by_wavefronts(maze, n, n_cells, scale, grid_n):
+    from dataclasses import replace
+    from paper_2505_20418_amd.md import MDRun
+    s = inputs.molten_nacl(n_cells, seed=9)
+    keep = np.random.default_rng(n).permutation(s.n_ions)[:n]
+    s = replace(s, box=s.box * scale, grid_spacing=s.box * scale / grid_n, pos=s.pos[keep] * scale,
+                vel=s.vel[keep], charges=s.charges[keep], species=s.species[keep],
+                masses=s.masses[keep])
+    print(f"case: short range by wavefronts ions={n} N={grid_n} scale={scale}", flush=True)
+    run = MDRun(s, tol=1e-4, flags=maze.MAZE_FLAG_ALLOW_NET_CHARGE)
+    F_ref, e_ref = oracle.bmh(s.pos, s.species, s.box, inputs.BMH_TABLE, inputs.BMH_CUTOFF)
+    F = run.f_sr.cpu().numpy()
+    assert np.abs(F - F_ref).max() <= 1e-10 * max(1.0, np.abs(F_ref).max())
+    assert abs(run.observables()["v_sr"] - e_ref) <= 1e-10 * abs(e_ref)
+    run.close()
