@@ -189,7 +189,125 @@ __global__ __launch_bounds__(kThreads) void k_bin_sort(int ntiles, int order,
   }
 }
 
+// The whole binning of a small system in one workgroup: cells, counts, starts,
+// tile order and the tile-ordered copies, with the counts and the order in LDS.
+// Each of the four passes above is a few microseconds of launch and latency on
+// such a system: 216 ions take 5.6 us and 512 take 7.7, where the four took 13
+// to 15 and three more launches. The limits are what the LDS of one workgroup
+// holds; at 4096 ions and 4096 tiles it is even with the four passes.
+constexpr int kBinSmallIons = 4096, kBinSmallTiles = 4096;
+constexpr int kBinIonsPerThread = kBinSmallIons / kScanThreads;
+constexpr int kBinTilesPerThread = kBinSmallTiles / kScanThreads;
+__global__ __launch_bounds__(kScanThreads) void k_bin_small(
+    const double* __restrict__ pos, const double* __restrict__ Q, int n, double box, double h,
+    int N, int ntx, int ntiles, int order, int32_t* __restrict__ ion_cell,
+    double* __restrict__ ion_t, int32_t* __restrict__ tile_start,
+    int32_t* __restrict__ sorted_idx, int32_t* __restrict__ s_cell, double* __restrict__ s_w,
+    double* __restrict__ s_Q, Scalars* sc) {
+  constexpr int W = kScanThreads / 64;
+  __shared__ int32_t count[kBinSmallTiles], sorted[kBinSmallIons], wsum[W];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  if (ctl_ld(&sc->err)) return;
+  for (int t = tid; t < ntiles; t += kScanThreads) count[t] = 0;
+  __syncthreads();
+  int tile[kBinIonsPerThread], slot[kBinIonsPerThread];
+  int bad = 0;
+#pragma unroll
+  for (int k = 0; k < kBinIonsPerThread; ++k) {
+    const int i = tid + k * kScanThreads;
+    tile[k] = -1;
+    if (i >= n) continue;
+    int at = 0;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      const double x = pos[3 * i + d];
+      int c = 0;
+      double t = 0.0;
+      if (isfinite(x)) cell_of(x, box, h, N, &c, &t);
+      else bad = 1;
+      ion_cell[3 * i + d] = c;
+      ion_t[3 * i + d] = t;
+      at = at * ntx + c / kTile;
+    }
+    tile[k] = at;
+    slot[k] = atomicAdd(&count[at], 1);
+  }
+  if (__syncthreads_or(bad)) {
+    if (tid == 0) ctl_st(&sc->err, 1);
+    return;
+  }
+  // exclusive scan, in place
+  int32_t v[kBinTilesPerThread], own = 0;
+#pragma unroll
+  for (int k = 0; k < kBinTilesPerThread; ++k) {
+    const int t = kBinTilesPerThread * tid + k;
+    v[k] = t < ntiles ? count[t] : 0;
+    own += v[k];
+  }
+  int32_t x = own;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int32_t y = __shfl_up(x, off, 64);
+    if (lane >= off) x += y;
+  }
+  if (lane == 63) wsum[w] = x;
+  __syncthreads();
+  int32_t run = x - own;
+#pragma unroll
+  for (int k = 0; k < W; ++k) run += k < w ? wsum[k] : 0;
+#pragma unroll
+  for (int k = 0; k < kBinTilesPerThread; ++k) {
+    const int t = kBinTilesPerThread * tid + k;
+    if (t < ntiles) {
+      count[t] = run;
+      tile_start[t] = run;
+    }
+    run += v[k];
+  }
+  if (tid == 0) tile_start[ntiles] = n;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kBinIonsPerThread; ++k)
+    if (tile[k] >= 0) sorted[count[tile[k]] + slot[k]] = tid + k * kScanThreads;
+  __syncthreads();
+  // an ion's place: the ions of its tile with a smaller index come before it
+  int at[kBinIonsPerThread];
+#pragma unroll
+  for (int k = 0; k < kBinIonsPerThread; ++k) {
+    if (tile[k] < 0) continue;
+    const int b = count[tile[k]], e = tile[k] + 1 < ntiles ? count[tile[k] + 1] : n;
+    int before = 0;
+    for (int j = b; j < e; ++j) before += sorted[j] < tid + k * kScanThreads ? 1 : 0;
+    at[k] = b + before;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kBinIonsPerThread; ++k)
+    if (tile[k] >= 0) sorted[at[k]] = tid + k * kScanThreads;
+  __syncthreads();
+  for (int s = tid; s < n; s += kScanThreads) {
+    const int ion = sorted[s];
+    sorted_idx[s] = ion;
+    s_Q[s] = Q[ion];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      s_cell[3 * s + d] = ion_cell[3 * ion + d];
+      double wt[kMaxOrder];
+      axis_weights(order, ion_t[3 * ion + d], wt);
+#pragma unroll
+      for (int m = 0; m < kMaxOrder; ++m)
+        if (m < order) s_w[(3 * s + d) * order + m] = wt[m];
+    }
+  }
+}
+
 hipError_t launch_bin(const DeviceState& d, const double* pos, hipStream_t st) {
+  if (d.n_ions <= kBinSmallIons && d.ntiles <= kBinSmallTiles) {
+    hipLaunchKernelGGL(k_bin_small, dim3(1), dim3(kScanThreads), 0, st, pos, (const double*)d.Q,
+                       d.n_ions, d.box, d.h, d.N, d.ntx, d.ntiles, d.order, d.ion_cell, d.ion_t,
+                       d.tile_start, d.sorted_idx, d.s_cell, d.s_w, d.s_Q, d.sc);
+    return hipGetLastError();
+  }
   const int nb = (d.n_ions + kThreads - 1) / kThreads;
   hipLaunchKernelGGL(k_bin_ions, dim3(nb), dim3(kThreads), 0, st, pos, d.n_ions, d.box, d.h,
                      d.N, d.ntx, d.ion_cell, d.ion_t, d.tile_count, d.sc);
@@ -381,59 +499,78 @@ hipError_t launch_spread(const DeviceState& d, hipStream_t st) {
 }
 
 // ---- force interpolation (equation "F_nostra") --------------------------------
-// One thread per ion in tile order (neighbouring threads read neighbouring
-// grid points); F_a = -k Q_a sum_n W(r_a - r_n) (phi_{n+e} - phi_{n-e}) / 2h.
-__global__ __launch_bounds__(kThreads) void k_gather(int n, int N, int order, double h,
-                                                     double coulomb_k,
+// The energy of the step, by one workgroup of the force kernels: the sum that
+// FIN_ENERGY takes, in the same order.
+struct EnergyJob {
+  const double* part;
+  int count;
+  double coulomb_k;
+  double* out;
+};
+__device__ __forceinline__ void energy_block(const EnergyJob& j, Scalars* sc, double* red) {
+  const double e = sum_partials(j.part, j.count, red);
+  if (threadIdx.x == 0) {
+    ctl_st(&sc->energy, 0.5 * j.coulomb_k * e);
+    if (j.out) *j.out = 0.5 * j.coulomb_k * e;
+  }
+}
+
+// Eight lanes per ion in tile order (neighbouring ions read neighbouring grid
+// points), a support point each at a time, added in the order of the points;
+// F_a = -k Q_a sum_n W(r_a - r_n) (phi_{n+e} - phi_{n-e}) / 2h. The last
+// workgroup takes the energy. Bound by latency on small systems: 216 ions 2.8
+// us (7.2 with one thread an ion, and FIN_ENERGY's launch).
+constexpr int kGatherLanes = 8;
+template <int ORDER>
+__global__ __launch_bounds__(kThreads) void k_gather(int n, int N, double h, double coulomb_k,
                                                      const int32_t* __restrict__ sorted_idx,
                                                      const int32_t* __restrict__ s_cell,
                                                      const double* __restrict__ s_w,
                                                      const double* __restrict__ s_Q,
                                                      const double* __restrict__ phi,
-                                                     double* __restrict__ forces,
-                                                     const Scalars* sc) {
+                                                     double* __restrict__ forces, EnergyJob ej,
+                                                     Scalars* sc) {
 #pragma clang fp contract(off)
-  const int s = blockIdx.x * kThreads + threadIdx.x;
-  if (s >= n || ctl_ld(&sc->err)) return;
-  const int off = (order == 2) ? 0 : 1;
-  int ix[kMaxOrder], iy[kMaxOrder], iz[kMaxOrder];
-  int ixm[kMaxOrder], ixp[kMaxOrder], iym[kMaxOrder], iyp[kMaxOrder], izm[kMaxOrder],
-      izp[kMaxOrder];
-  const double* w = s_w + (size_t)3 * s * order;
-  for (int m = 0; m < order; ++m) {
-    auto wrap = [N](int v) { return v < 0 ? v + N : (v >= N ? v - N : v); };
-    ix[m] = wrap(s_cell[3 * s] - off + m);
-    iy[m] = wrap(s_cell[3 * s + 1] - off + m);
-    iz[m] = wrap(s_cell[3 * s + 2] - off + m);
-    ixm[m] = wrap(ix[m] - 1);
-    ixp[m] = wrap(ix[m] + 1);
-    iym[m] = wrap(iy[m] - 1);
-    iyp[m] = wrap(iy[m] + 1);
-    izm[m] = wrap(iz[m] - 1);
-    izp[m] = wrap(iz[m] + 1);
+  __shared__ double red[8];
+  if (ctl_ld(&sc->err)) return;
+  if (blockIdx.x == gridDim.x - 1) {
+    energy_block(ej, sc, red);
+    return;
   }
+  constexpr int kPoints = ORDER * ORDER * ORDER;
+  const int gt = blockIdx.x * kThreads + threadIdx.x;
+  const int lane = gt % kGatherLanes, at = gt / kGatherLanes, s = min(at, n - 1);
+  const int off = (ORDER == 2) ? 0 : 1;
+  auto wrap = [N](int v) { return v < 0 ? v + N : (v >= N ? v - N : v); };
+  const int cx = s_cell[3 * s] - off, cy = s_cell[3 * s + 1] - off, cz = s_cell[3 * s + 2] - off;
+  const double* w = s_w + (size_t)3 * s * ORDER;
   const long long NN = (long long)N * N;
   const double two_h = 2.0 * h;
   double acc[3] = {0.0, 0.0, 0.0};
-  for (int a = 0; a < order; ++a)
-    for (int b = 0; b < order; ++b)
-      for (int c = 0; c < order; ++c) {
-        double W = w[a] * w[order + b];
-        W = W * w[2 * order + c];
-        const long long I = ix[a] * NN, J = (long long)iy[b] * N;
-        const double dx = (phi[ixp[a] * NN + J + iz[c]] - phi[ixm[a] * NN + J + iz[c]]) / two_h;
-        const double dy = (phi[I + (long long)iyp[b] * N + iz[c]] -
-                           phi[I + (long long)iym[b] * N + iz[c]]) / two_h;
-        const double dz = (phi[I + J + izp[c]] - phi[I + J + izm[c]]) / two_h;
-        acc[0] += W * dx;
-        acc[1] += W * dy;
-        acc[2] += W * dz;
-      }
-  const int ion = sorted_idx[s];
-  const double kq = -coulomb_k * s_Q[s];
-  forces[3 * ion + 0] = kq * acc[0];
-  forces[3 * ion + 1] = kq * acc[1];
-  forces[3 * ion + 2] = kq * acc[2];
+#pragma unroll 1
+  for (int q0 = 0; q0 < kPoints; q0 += kGatherLanes) {
+    const int q = q0 + lane;
+    const int a = q / (ORDER * ORDER), b = (q / ORDER) % ORDER, c = q % ORDER;
+    double W = w[a] * w[ORDER + b];
+    W = W * w[2 * ORDER + c];
+    const int ix = wrap(cx + a), iy = wrap(cy + b), iz = wrap(cz + c);
+    const long long I = ix * NN, J = (long long)iy * N;
+    const double dx =
+        (phi[wrap(ix + 1) * NN + J + iz] - phi[wrap(ix - 1) * NN + J + iz]) / two_h;
+    const double dy =
+        (phi[I + (long long)wrap(iy + 1) * N + iz] - phi[I + (long long)wrap(iy - 1) * N + iz]) /
+        two_h;
+    const double dz = (phi[I + J + wrap(iz + 1)] - phi[I + J + wrap(iz - 1)]) / two_h;
+    const double v[3] = {W * dx, W * dy, W * dz};
+#pragma unroll
+    for (int j = 0; j < kGatherLanes; ++j)
+#pragma unroll
+      for (int d = 0; d < 3; ++d) acc[d] += __shfl(v[d], j, kGatherLanes);
+  }
+  if (at < n && lane < 3) {
+    const double kq = -coulomb_k * s_Q[s];
+    forces[3 * sorted_idx[s] + lane] = kq * (lane == 0 ? acc[0] : lane == 1 ? acc[1] : acc[2]);
+  }
 }
 
 // ---- alternative force (equation "F_Benoit") --------------------------------
@@ -461,11 +598,17 @@ __global__ __launch_bounds__(kThreads) void k_gather_wg(int n, int N, int order,
                                                         const double* __restrict__ s_Q,
                                                         const double* __restrict__ ion_t,
                                                         const double* __restrict__ phi,
-                                                        double* __restrict__ forces,
-                                                        const Scalars* sc) {
+                                                        double* __restrict__ forces, EnergyJob ej,
+                                                        Scalars* sc) {
 #pragma clang fp contract(off)
+  __shared__ double red[8];
+  if (ctl_ld(&sc->err)) return;
+  if (blockIdx.x == gridDim.x - 1) {
+    energy_block(ej, sc, red);
+    return;
+  }
   const int s = blockIdx.x * kThreads + threadIdx.x;
-  if (s >= n || ctl_ld(&sc->err)) return;
+  if (s >= n) return;
   const int ion = sorted_idx[s];
   const int off = (order == 2) ? 0 : 1;
   const double* w = s_w + (size_t)3 * s * order;
@@ -504,17 +647,27 @@ __global__ __launch_bounds__(kThreads) void k_gather_wg(int n, int N, int order,
 }
 
 hipError_t launch_gather(const DeviceState& d, const double* phi, double coulomb_k,
-                         double* forces, hipStream_t st) {
-  const int nb = (d.n_ions + kThreads - 1) / kThreads;
+                         double* forces, double* energy_out, hipStream_t st) {
+  if (!forces)
+    return launch_finalize(d, FIN_ENERGY, update_blocks(d.G), 0.0, 0.0, coulomb_k, energy_out, 0, 0,
+                           st);
+  const EnergyJob ej{d.part + (size_t)SL_ENERGY * d.part_stride, update_blocks(d.G), coulomb_k,
+                     energy_out};
   if (d.weight_gradient_force) {
-    hipLaunchKernelGGL(k_gather_wg, dim3(nb), dim3(kThreads), 0, st, d.n_ions, d.N, d.order, d.h,
-                       coulomb_k, d.sorted_idx, d.s_cell, d.s_w, d.s_Q, (const double*)d.ion_t,
-                       phi, forces, (const Scalars*)d.sc);
+    const int nb = (d.n_ions + kThreads - 1) / kThreads;
+    hipLaunchKernelGGL(k_gather_wg, dim3(nb + 1), dim3(kThreads), 0, st, d.n_ions, d.N, d.order,
+                       d.h, coulomb_k, d.sorted_idx, d.s_cell, d.s_w, d.s_Q,
+                       (const double*)d.ion_t, phi, forces, ej, d.sc);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL(k_gather, dim3(nb), dim3(kThreads), 0, st, d.n_ions, d.N, d.order, d.h,
-                     coulomb_k, d.sorted_idx, d.s_cell, d.s_w, d.s_Q, phi, forces,
-                     (const Scalars*)d.sc);
+  const long long nl = (long long)d.n_ions * kGatherLanes;
+  const dim3 grid((unsigned)((nl + kThreads - 1) / kThreads) + 1);
+  if (d.order == 2)
+    hipLaunchKernelGGL(k_gather<2>, grid, dim3(kThreads), 0, st, d.n_ions, d.N, d.h, coulomb_k,
+                       d.sorted_idx, d.s_cell, d.s_w, d.s_Q, phi, forces, ej, d.sc);
+  else
+    hipLaunchKernelGGL(k_gather<4>, grid, dim3(kThreads), 0, st, d.n_ions, d.N, d.h, coulomb_k,
+                       d.sorted_idx, d.s_cell, d.s_w, d.s_Q, phi, forces, ej, d.sc);
   return hipGetLastError();
 }
 

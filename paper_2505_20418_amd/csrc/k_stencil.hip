@@ -250,6 +250,31 @@ __device__ __forceinline__ T nbr_sum(T xm, T xp, T ym, T yp, T zm, T zp) {
   return ((xm + xp) + (ym + yp)) + (zm + zp);
 }
 
+// The mean charge of a right-hand side: from the scalars, or (count > 0) from
+// the spread's partials, then stored by workgroup 0.
+struct ChargeSum {
+  const double* part;
+  int count;
+  long long G;
+  Scalars* out;
+  double sum;
+
+  __device__ double mean(const Scalars* sc, double* red) {
+    if (count == 0) return ctl_ld(&sc->qbar);
+    sum = sum_partials(part, count, red);
+    return sum / (double)G;
+  }
+  __device__ void store() const {
+    if (count == 0) return;
+    ctl_st(&out->qsum, sum);
+    ctl_st(&out->qbar, sum / (double)G);
+  }
+};
+static ChargeSum charge_sum(const DeviceState& d) {
+  return {d.part + (size_t)SL_QSUM * d.part_stride, d.ntiles <= kInlineQsum ? d.ntiles : 0, d.G,
+          d.sc, 0.0};
+}
+
 // ---------------------------------------------------------------------------
 // Right-hand side of the SHAKE system (Section 2, equations "SHAKE" and
 // "SHAKEy"): phi_p = 2 phi^k - phi^{k-1}, sigma_p = (h/4pi) M phi_p + (q - qbar),
@@ -272,11 +297,12 @@ struct OpRhsMaze {
   int parity;
   const Scalars* sc;
   double c1;    // h / (4 pi)
+  ChargeSum q_;
   double qbar;
 
   __device__ bool skip() const { return ctl_ld(&sc->err) != 0; }
-  __device__ bool prepare(double*) {
-    qbar = ctl_ld(&sc->qbar);
+  __device__ bool prepare(double* red) {
+    qbar = q_.mean(sc, red);
     return true;
   }
   static constexpr int KS = 1;
@@ -315,7 +341,7 @@ struct OpRhsMaze {
     const int s[7] = {SL_PHIP, SL_QQ, SL_RR0, SL_RMAX0, SL_XSUM, SL_TRR, SL_TMAX};
     return s[i];
   }
-  __device__ void finish_wg0() const {}
+  __device__ void finish_wg0() const { q_.store(); }
 };
 
 // ---------------------------------------------------------------------------
@@ -341,11 +367,12 @@ struct OpRhsPoisson {
   const Scalars* sc;
   int guess;
   double c4;    // -(4 pi / h)
+  ChargeSum q_;
   double qbar;
 
   __device__ bool skip() const { return ctl_ld(&sc->err) != 0; }
-  __device__ bool prepare(double*) {
-    qbar = ctl_ld(&sc->qbar);
+  __device__ bool prepare(double* red) {
+    qbar = q_.mean(sc, red);
     return true;
   }
   static constexpr int KS = 1;
@@ -383,7 +410,7 @@ struct OpRhsPoisson {
     const int s[7] = {SL_PHIP, SL_QQ, SL_RR0, SL_RMAX0, SL_XSUM, SL_TRR, SL_TMAX};
     return s[i];
   }
-  __device__ void finish_wg0() const {}
+  __device__ void finish_wg0() const { q_.store(); }
 };
 
 // ---------------------------------------------------------------------------
@@ -563,11 +590,11 @@ hipError_t launch_rhs_maze(const DeviceState& d, const MarchGeom& g, bool mixed,
   const double c1 = d.h / (4.0 * M_PI);
   if (mixed) {
     OpRhsMaze<true> op{d.phi_cur, d.phi_prev, d.y, d.q, d.sigma, nullptr, d.r32,
-                       d.part, d.part_stride, 0, d.sc, c1, 0.0};
+                       d.part, d.part_stride, 0, d.sc, c1, charge_sum(d), 0.0};
     return launch_march(op, g, st);
   }
   OpRhsMaze<false> op{d.phi_cur, d.phi_prev, d.y, d.q, d.sigma, d.r, nullptr,
-                      d.part, d.part_stride, 0, d.sc, c1, 0.0};
+                      d.part, d.part_stride, 0, d.sc, c1, charge_sum(d), 0.0};
   return launch_march(op, g, st);
 }
 
@@ -576,11 +603,11 @@ hipError_t launch_rhs_poisson(const DeviceState& d, const MarchGeom& g, int gues
   const double c4 = -(4.0 * M_PI / d.h);
   if (mixed) {
     OpRhsPoisson<true> op{d.phi_cur, d.phi_prev, d.q, d.sigma, x, nullptr, d.r32,
-                          d.part, d.part_stride, 0, d.sc, guess, c4, 0.0};
+                          d.part, d.part_stride, 0, d.sc, guess, c4, charge_sum(d), 0.0};
     return launch_march(op, g, st);
   }
   OpRhsPoisson<false> op{d.phi_cur, d.phi_prev, d.q, d.sigma, x, d.r, nullptr,
-                         d.part, d.part_stride, 0, d.sc, guess, c4, 0.0};
+                         d.part, d.part_stride, 0, d.sc, guess, c4, charge_sum(d), 0.0};
   return launch_march(op, g, st);
 }
 

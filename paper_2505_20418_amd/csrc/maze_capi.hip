@@ -1491,7 +1491,8 @@ static int assign(maze_session* s, const double* pos) {
   DeviceState& d = s->d;
   HIP_TRY(launch_bin(d, pos, s->stream));
   HIP_TRY(launch_spread(d, s->stream));
-  HIP_TRY(launch_finalize(d, FIN_QSUM, d.ntiles, 0.0, 0.0, 0.0, nullptr, 0, 0, s->stream));
+  if (d.ntiles > kInlineQsum)
+    HIP_TRY(launch_finalize(d, FIN_QSUM, d.ntiles, 0.0, 0.0, 0.0, nullptr, 0, 0, s->stream));
   return MAZE_OK;
 }
 
@@ -1518,9 +1519,7 @@ static int direct_solve(maze_session* s, int guess, const double* pos, double* x
   }
   if (rcs[0] == MAZE_E_NONFINITE) return recover_error(s);
   HIP_TRY(launch_project(d, x, field, s->stream));
-  HIP_TRY(launch_finalize(d, FIN_ENERGY, update_blocks(d.G), 0.0, 0.0, s->cfg.coulomb_k,
-                          energy, 0, 0, s->stream));
-  if (forces) HIP_TRY(launch_gather(d, x, s->cfg.coulomb_k, forces, s->stream));
+  HIP_TRY(launch_gather(d, x, s->cfg.coulomb_k, forces, energy, s->stream));
   return MAZE_OK;
 }
 
@@ -1579,10 +1578,8 @@ static int step_multi(std::vector<maze_session*>& ss, const double* const* pos,
     }
     s->last_iters = s->iters;
     HIP_TRY(launch_update(d, field ? field[i] : nullptr, s->stream));
-    HIP_TRY(launch_finalize(d, FIN_ENERGY, update_blocks(d.G), 0.0, 0.0, s->cfg.coulomb_k,
-                            energies ? energies[i] : nullptr, 0, 0, s->stream));
-    if (forces && forces[i])
-      HIP_TRY(launch_gather(d, d.phi_prev, s->cfg.coulomb_k, forces[i], s->stream));
+    HIP_TRY(launch_gather(d, d.phi_prev, s->cfg.coulomb_k, forces ? forces[i] : nullptr,
+                          energies ? energies[i] : nullptr, s->stream));
     std::swap(d.phi_cur, d.phi_prev);
     s->step += 1;
   }
@@ -2113,10 +2110,8 @@ int batch_finish(maze_batch* b, BatchJob& j, long long next_poll) {
   DeviceState& d = s->d;
   hipStream_t st = s->stream;
   HIP_TRY(launch_update(d, nullptr, st));
-  HIP_TRY(launch_finalize(d, FIN_ENERGY, update_blocks(d.G), 0.0, 0.0, s->cfg.coulomb_k,
-                          j.has_md ? j.md.scalars_dev + 6 : j.energy, 0, 0, st));
-  double* F = j.has_md ? j.md.f_es_dev : j.forces;
-  if (F) HIP_TRY(launch_gather(d, d.phi_prev, s->cfg.coulomb_k, F, st));
+  HIP_TRY(launch_gather(d, d.phi_prev, s->cfg.coulomb_k, j.has_md ? j.md.f_es_dev : j.forces,
+                        j.has_md ? j.md.scalars_dev + 6 : j.energy, st));
   std::swap(d.phi_cur, d.phi_prev);
   s->step += 1;
   if (j.has_md) {

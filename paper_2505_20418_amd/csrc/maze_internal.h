@@ -222,8 +222,15 @@ hipError_t launch_bin(const DeviceState& d, const double* pos, hipStream_t st);
 hipError_t launch_spread(const DeviceState& d, hipStream_t st);
 // Builds d.cand (once per session, before the first spread).
 hipError_t launch_cand_table(const DeviceState& d, hipStream_t st);
+// Forces (if wanted) and the energy of the field whose update or projection
+// was queued before.
 hipError_t launch_gather(const DeviceState& d, const double* phi, double coulomb_k,
-                         double* forces, hipStream_t st);
+                         double* forces, double* energy_out, hipStream_t st);
+
+// The right-hand sides of grids of at most this many tiles sum the charge
+// themselves (every workgroup the spread's partials, in FIN_QSUM's order); on
+// larger ones that costs each of many workgroups more than FIN_QSUM's launch.
+constexpr int kInlineQsum = 1024;
 
 // finalize modes (single-workgroup reductions of partial slots into Scalars)
 enum FinalizeMode : int {

@@ -224,3 +224,31 @@ def test_sstep_full_parity_128_mixed(maze):
         assert eF <= 1e-4 and eE <= 1e-6
     g.close()
     o.close()
+
+
+# the one-workgroup binning up to 4096 ions and 4096 tiles (128^3), the four
+# passes beyond; the charge summed by the right-hand side up to 1024 tiles (80^3
+# has 1000, 88^3 1331); eight lanes to an ion in the force interpolation
+@pytest.mark.parametrize("n,N,order", [
+    (1, 16, 2), (7, 18, 4), (1023, 33, 4), (1025, 80, 2), (4096, 32, 4), (4097, 32, 2),
+    (300, 88, 4), (64, 128, 2), (64, 129, 2)])
+def test_binning_charge_and_interpolation_by_size(maze, n, N, order):
+    rng = np.random.default_rng(1000 * N + n)
+    box = 0.4 * N
+    pos = rng.uniform(-0.2 * box, 1.2 * box, (n, 3))
+    pos[: n // 4] = pos[0] + rng.uniform(0, 1.0, (n // 4, 3))  # a crowded tile
+    q = rng.uniform(-1.0, 1.0, n)
+    print(f"case: binning n={n} N={N} order={order}", flush=True)
+    g = maze.Session(dev(q), dev(pos), box, box / N, tol=1e-6, order=order,
+                     flags=maze.MAZE_FLAG_ALLOW_NET_CHARGE)
+    out = g.step(dev(pos), want_field=True)
+    assert out["status"] == 0 and g.N == N
+    ref = oracle.spread_raw(pos, q, box, N, order)
+    Q = g.grid(GRID_Q).cpu().numpy()
+    assert np.abs(Q - ref).max() <= 1e-13 * max(1.0, np.abs(ref).max())
+    assert abs(out["stats"]["net_charge"] - q.sum()) <= 1e-12 * max(1.0, np.abs(q).sum())
+    phi = out["field"].cpu().numpy()
+    assert rel(out["forces"], oracle.gather(pos, q, box, phi, order)) <= 1e-12
+    e = oracle.energy(phi, ref - ref.mean())
+    assert abs(out["energy"].item() - e) <= 1e-10 * abs(e)
+    g.close()
