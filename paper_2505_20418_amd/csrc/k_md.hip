@@ -169,6 +169,9 @@ struct BmhWave {
   }
 };
 
+// The kernels that end an MD step are queued before the outcome of its solve is
+// known; after an error (Scalars::err) they change nothing.
+
 // The coefficients and the shifts into LDS; the caller waits.
 __device__ __forceinline__ void bmh_table(const MdParams& p, double* tab) {
   const int t = threadIdx.x;
@@ -179,9 +182,11 @@ __device__ __forceinline__ void bmh_table(const MdParams& p, double* tab) {
 // All pairs: every j, staged through LDS for the workgroup's four ions.
 __global__ __launch_bounds__(kThreads) void k_md_bmh(MdParams p, const double* __restrict__ pos,
                                                      const int32_t* __restrict__ species,
-                                                     double* __restrict__ f_sr, double* part_e) {
+                                                     double* __restrict__ f_sr, double* part_e,
+                                                     const Scalars* sc) {
   __shared__ double sx[kThreads], sy[kThreads], sz[kThreads], tab[18], red[8];
   __shared__ BmhLds lds[kBmhWaves];
+  if (ctl_ld(&sc->err)) return;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int s = __builtin_amdgcn_readfirstlane(blockIdx.x * kBmhWaves + w);
   const int i = min(s, p.n - 1);
@@ -228,11 +233,12 @@ __global__ __launch_bounds__(kThreads) void k_md_bmh_tiles(MdParams p, BmhTiles 
                                                            const double* __restrict__ pos,
                                                            const int32_t* __restrict__ species,
                                                            double* __restrict__ f_sr,
-                                                           double* e_part) {
+                                                           double* e_part, const Scalars* sc) {
   __shared__ double tab[18], red[8];
   __shared__ BmhLds lds[kBmhWaves];
   __shared__ int list[kBmhWaves][kBmhList];
   __shared__ uint8_t list_cls[kBmhWaves][kBmhList];
+  if (ctl_ld(&sc->err)) return;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int s = __builtin_amdgcn_readfirstlane(blockIdx.x * kBmhWaves + w);
   bmh_table(p, tab);
@@ -331,8 +337,10 @@ __global__ __launch_bounds__(kThreads) void k_md_kick2(MdParams p, const double*
                                                        const double* __restrict__ f_es,
                                                        const double* __restrict__ f_sr,
                                                        const double* x_old, const double* f_old,
-                                                       int do_kick, double* part, int nb) {
+                                                       int do_kick, double* part, int nb,
+                                                       const Scalars* sc) {
   __shared__ double red[8];
+  if (ctl_ld(&sc->err)) return;
   const int i = blockIdx.x * kThreads + threadIdx.x;
   double ke = 0, w = 0, px = 0, py = 0, pz = 0;
   if (i < p.n) {
@@ -381,8 +389,9 @@ __global__ __launch_bounds__(kThreads) void k_md_kick2(MdParams p, const double*
 
 __global__ __launch_bounds__(kThreads) void k_md_finish(const double* part, int nb,
                                                         const double* e_part, int ne, int prime,
-                                                        double* scalars) {
+                                                        double* scalars, const Scalars* sc) {
   __shared__ double red[8];
+  if (ctl_ld(&sc->err)) return;
   const double e_sr = sum_partials(e_part, ne, red);
   const double ke = sum_partials(part + 1 * nb, nb, red);
   const double w = sum_partials(part + 2 * nb, nb, red);
@@ -427,10 +436,12 @@ hipError_t launch_md_bmh(const maze_md_state& md, const DeviceState& d, hipStrea
   if (R > 0) {
     BmhTiles t{d.tile_start, d.sorted_idx, d.s_cell, d.ntx, R};
     hipLaunchKernelGGL(k_md_bmh_tiles, grid, dim3(kThreads), 0, st, p, t,
-                       (const double*)md.pos_dev, md.species_dev, md.f_sr_dev, d.md_epart);
+                       (const double*)md.pos_dev, md.species_dev, md.f_sr_dev, d.md_epart,
+                       (const Scalars*)d.sc);
   } else {
     hipLaunchKernelGGL(k_md_bmh, grid, dim3(kThreads), 0, st, p, (const double*)md.pos_dev,
-                       md.species_dev, md.f_sr_dev, d.md_epart);
+                       md.species_dev, md.f_sr_dev, d.md_epart,
+                       (const Scalars*)d.sc);
   }
   return hipGetLastError();
 }
@@ -443,10 +454,11 @@ static hipError_t md_finish(const maze_md_state& md, const DeviceState& d, int d
   hipLaunchKernelGGL(k_md_kick2, dim3(nb), dim3(kThreads), 0, st, p, (const double*)md.pos_dev,
                      md.vel_dev, md.mass_dev, (const double*)md.f_es_dev,
                      (const double*)md.f_sr_dev, (const double*)md.scratch_dev,
-                     (const double*)(md.scratch_dev + 3 * (size_t)n), do_kick, part, nb);
+                     (const double*)(md.scratch_dev + 3 * (size_t)n), do_kick, part, nb,
+                     (const Scalars*)d.sc);
   hipLaunchKernelGGL(k_md_finish, dim3(1), dim3(kThreads), 0, st, (const double*)part, nb,
                      (const double*)d.md_epart, md_energy_partials(md.n_ions),
-                     do_kick ? 0 : 1, md.scalars_dev);
+                     do_kick ? 0 : 1, md.scalars_dev, (const Scalars*)d.sc);
   return hipGetLastError();
 }
 

@@ -832,6 +832,24 @@ __global__ __launch_bounds__(kThreads) void k_finalize(int mode, int count, long
         ctl_st(&sc->done, 0);
       }
     }
+  } else if (mode == FIN_INNER_END) {
+    // The end of the step's first inner solve, decided as the host decides
+    // later ones (imax: the step's iterations): where another must follow,
+    // the kernels already queued behind it do nothing.
+    if (ctl_ld(&sc->err) != 0 || ctl_ld(&sc->done) == 4) return;
+    const double xs = sum_partials(slot(SL_XSUM), count, red);
+    const double trr = sum_partials(slot(SL_TRR), count, red);
+    const double tmx = max_partials(slot(SL_TMAX), count, red);
+    if (threadIdx.x == 0) {
+      ctl_st(&sc->xbar, xs / (double)G);
+      ctl_st(&sc->true_rr, trr);
+      ctl_st(&sc->true_max, tmx);
+      const double res = (ctl_ld(&sc->norm) == MAZE_NORM_ABSMAX) ? tmx : sqrt(trr);
+      const int it = ctl_ld(&sc->iters);
+      const bool last = res <= ctl_ld(&sc->thr_outer) || it >= imax ||
+                        (it == 0 && ctl_ld(&sc->done) == 2);
+      if (!last) ctl_st(&sc->err, kErrMore);
+    }
   } else if (mode == FIN_INNER_START) {
     if (threadIdx.x == 0) {
       ctl_st(&sc->thr, param);
@@ -903,7 +921,8 @@ hipError_t launch_finalize(const DeviceState& d, int mode, int count, double tol
 __global__ __launch_bounds__(kThreads) void k_add_correction(long long G, double* x,
                                                              const float* __restrict__ e,
                                                              const Scalars* sc) {
-  if (ctl_ld(&sc->err)) return;
+  // done 4: there was no inner solve
+  if (ctl_ld(&sc->err) || ctl_ld(&sc->done) == 4) return;
   const long long base = (long long)blockIdx.x * kThreads * kElemPerThread + threadIdx.x;
 #pragma unroll
   for (int j = 0; j < kElemPerThread; ++j) {

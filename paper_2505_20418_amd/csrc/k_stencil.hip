@@ -515,7 +515,10 @@ struct OpResidual {
   int parity;
   const Scalars* sc;
 
-  __device__ bool skip() const { return ctl_ld(&sc->err) != 0; }
+  // done 4: there was no inner solve to end
+  __device__ bool skip() const {
+    return ctl_ld(&sc->err) != 0 || (WRITE32 && ctl_ld(&sc->done) == 4);
+  }
   __device__ bool prepare(double*) { return true; }
   static constexpr int KS = 1;
   __device__ void load(long long g, double v[1]) const { v[0] = x[g]; }

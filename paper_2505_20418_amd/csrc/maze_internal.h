@@ -134,6 +134,7 @@ constexpr size_t kPersistSlotBytes = sizeof(double) * kPersistSlots;
 constexpr uint32_t kPersistEmpty32 = 0xffa5a5a5u;
 constexpr unsigned long long kPersistEmpty = 0xfff4dead4d415a45ull;
 constexpr int kErrAborted = 2;         // Scalars::err: a resident solve gave up waiting
+constexpr int kErrMore = 3;            // another inner solve is needed (FIN_INNER_END)
 struct PersistGeom {
   int N = 0;
   int ncx = 0, ncy = 0;
@@ -238,6 +239,7 @@ enum FinalizeMode : int {
   FIN_SOLVE_START,   // qnorm, thr, pbar; resets it/done/iters
   FIN_SOLVE_END,     // xbar (from SL_XSUM), true residual
   FIN_ENERGY,        // energy from SL_ENERGY, writes energy_out
+  FIN_INNER_END,     // FIN_SOLVE_END of a first inner solve; err = kErrMore if not the last
   FIN_INNER_START,   // mixed inner solve: thr from `param`, resets counters
   FIN_INNER_FIRST,   // first inner solve of a mixed step: thr from the true
                      // residual (done = 4 if it already meets thr)

@@ -128,3 +128,55 @@ def test_solve_that_gives_up_is_repeated(maze, monkeypatch, prec, tol):
     batch.close()
     for x in (ref, alone, inbatch, other, flight):
         x.close()
+
+
+# one inner solve, several, none (a right-hand side within a loose tolerance), a
+# step that may not converge, and FP64
+@pytest.mark.parametrize("prec,tol,max_iter", [
+    (0, 1e-10, 100000), (0, 1e-10, 5), (1, 1e-6, 100000), (1, 1e-12, 100000), (1, 0.5, 100000),
+    (1, 1e-10, 9)])
+@pytest.mark.parametrize("spin", [None, "0"])
+def test_steps_queued_ahead_are_those_of_a_batch(maze, monkeypatch, prec, tol, max_iter, spin):
+    """A step alone is queued whole before its solve has ended; in a batch the
+    host waits for each stage. Both end in the same bits, where the solve ends
+    as foreseen, where it needs more, and where it gives up and is repeated."""
+    from paper_2505_20418_amd.md import MDRun, step_many
+    print(f"case: queued ahead precision={prec} tol={tol} max_iter={max_iter} spin={spin}",
+          flush=True)
+    s = inputs.molten_nacl(2, seed=21)
+    make_run = lambda: MDRun(s, tol=tol, precision=prec, max_iter=max_iter, gamma=0.01,
+                             temperature=1000.0, seed=5)
+    alone, a, b = make_run(), make_run(), make_run()
+    if spin is not None:
+        monkeypatch.setenv("MAZE_PERSIST_SPIN", spin)
+    for _ in range(3):
+        _, got = alone.step(want_stats=True)
+        _, want = step_many([a, b])
+        for x in (a, b):
+            for name in ("pos", "vel", "f_es", "f_sr", "scalars"):
+                assert torch.equal(getattr(alone, name), getattr(x, name)), name
+        assert torch.equal(alone.session.grid(maze.GRID_PHI), a.session.grid(maze.GRID_PHI))
+        assert got == want[0], (got, want[0])
+    for x in (alone, a, b):
+        x.close()
+
+
+def test_queued_ahead_step_with_bad_positions_changes_nothing(maze):
+    from paper_2505_20418_amd.md import MDRun
+    s = inputs.molten_nacl(2, seed=22)
+    run = MDRun(s, tol=1e-6, precision=1)
+    run.step()
+    keep = {k: getattr(run, k).clone() for k in ("f_es", "f_sr", "scalars")}
+    phi, pos = run.session.grid(maze.GRID_PHI), run.pos.clone()
+    vel = run.vel.clone()
+    run.pos[3, 1] = float("nan")
+    with pytest.raises(maze.MazeError):
+        run.step()
+    for k, v in keep.items():
+        assert torch.equal(getattr(run, k), v), k
+    assert torch.equal(run.session.grid(maze.GRID_PHI), phi)
+    run.pos.copy_(pos)
+    run.vel.copy_(vel)
+    run.step()
+    assert torch.isfinite(run.f_es).all() and torch.isfinite(run.scalars).all()
+    run.close()
