@@ -207,10 +207,13 @@ static int part_stride_for(const DeviceState& d, const MarchGeom& g, const Sweep
 // two-iteration form could spare: 128^3 FP64 MD step 5.20 ms launched in that
 // form, 2.6 resident). MAZE_PERSIST=0 in the environment keeps to launched
 // kernels.
-static PersistGeom persist_geom_of(const maze_config* c, int N) {
+static PersistGeom persist_geom(const maze_config* c, int N) {
   const char* e = std::getenv("MAZE_PERSIST");
-  if ((e && e[0] == '0') || (c->flags & MAZE_FLAG_MULTIGRID)) return {};
+  if (e && e[0] == '0') return {};
   return make_persist_geom(N, c->precision == MAZE_MIXED);
+}
+static PersistGeom persist_geom_of(const maze_config* c, int N) {
+  return (c->flags & MAZE_FLAG_MULTIGRID) ? PersistGeom{} : persist_geom(c, N);
 }
 
 struct Layout {
@@ -269,7 +272,9 @@ static Layout layout_for(const maze_config* c, int N, int* ntx_out, int* ntiles_
   L.add(sizeof(double) * (n + 1));        // 23 md_epart
   L.add(sizeof(double) * kHistCap);       // 24 residual history
   L.add(sizeof(int32_t) * (size_t)ntx * (1 + kMaxCandAxis));  // 25 spreading candidates
-  L.add(persist_bytes(persist_geom_of(c, N), mixed));          // 26 resident solves
+  // 26 resident solves; with multigrid too, which does not use it, so that the
+  // flag only ever adds to what maze_device_bytes reports
+  L.add(persist_bytes(persist_geom(c, N), c->precision == MAZE_MIXED));
   if (mg) {
     int Ns[kMgMaxLevels];
     const int levels = mg_plan(N, Ns, kMgMaxLevels);
