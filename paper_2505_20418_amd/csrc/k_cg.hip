@@ -591,7 +591,6 @@ SweepArgs<T> make_sweep_args(const DeviceState& d, T* x, int nprev_first, int np
   a.nprev_sweep = nprev_sweep;
   a.zero_x = zero_x ? 1 : 0;
   a.hist_cap = d.hist_cap;
-  a.res = d.res;
   return a;
 }
 template SweepArgs<float> make_sweep_args<float>(const DeviceState&, float*, int, int, bool);

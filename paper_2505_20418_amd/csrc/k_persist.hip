@@ -686,6 +686,16 @@ int persist_resident(const PersistGeom& g, bool fp32, bool batch, int cus) {
   return per * cus;
 }
 
+// The sweep's arguments and the session's exchange scratch.
+template <typename T>
+SweepArgs<T> persist_args(const DeviceState& d, T* x, int nprev_first, bool zero_x) {
+  SweepArgs<T> a = make_sweep_args<T>(d, x, nprev_first, 0, zero_x);
+  a.res = d.res;
+  return a;
+}
+template SweepArgs<float> persist_args<float>(const DeviceState&, float*, int, bool);
+template SweepArgs<double> persist_args<double>(const DeviceState&, double*, int, bool);
+
 hipError_t launch_persist(const DeviceState& d, const PersistGeom& g, void* x, bool fp32,
                           bool zero_x, int nprev_first, unsigned spin, hipStream_t st) {
   const void* fn = kernel_fn(fp32, false, g.cls);
@@ -698,10 +708,10 @@ hipError_t launch_persist(const DeviceState& d, const PersistGeom& g, void* x, b
   SweepArgs<double> ad;
   void* args[3] = {nullptr, &gg, &spin};
   if (fp32) {
-    af = make_sweep_args<float>(d, (float*)x, nprev_first, 0, zero_x);
+    af = persist_args<float>(d, (float*)x, nprev_first, zero_x);
     args[0] = &af;
   } else {
-    ad = make_sweep_args<double>(d, (double*)x, nprev_first, 0, zero_x);
+    ad = persist_args<double>(d, (double*)x, nprev_first, zero_x);
     args[0] = &ad;
   }
   return hipLaunchKernel(fn, dim3(g.nwg), dim3(kClasses[g.cls].nt), args, lds, st);

@@ -869,10 +869,10 @@ static int queue_persist(const std::vector<int>& idx, F job, bool fp32, bool zer
     hg[q] = g;
     if (fp32)
       ((SweepArgs<float>*)(H + t->o_args))[q] =
-          make_sweep_args<float>(s->d, (float*)j.x, s->geom.nwg, 0, zero_x);
+          persist_args<float>(s->d, (float*)j.x, s->geom.nwg, zero_x);
     else
       ((SweepArgs<double>*)(H + t->o_args))[q] =
-          make_sweep_args<double>(s->d, (double*)j.x, s->geom.nwg, 0, zero_x);
+          persist_args<double>(s->d, (double*)j.x, s->geom.nwg, zero_x);
   }
   hw[wpos++] = grps.back().nwg;
   HIP_TRY(hipMemcpyAsync(t->dev, H, t->o_geom2, hipMemcpyHostToDevice, st));

@@ -276,7 +276,7 @@ struct SweepArgs {
   int par_flip;    // batched launches: this session's parity is the launch's
                    // parity XOR par_flip (sessions that joined at different
                    // iterations share one launch)
-  void* res;       // resident solves: DeviceState::res
+  void* res = nullptr;  // resident solves: DeviceState::res
 };
 
 template <typename T>
@@ -351,6 +351,8 @@ PersistGeom make_persist_geom(int N, bool fp32);
 size_t persist_bytes(const PersistGeom& g, bool fp32);  // of DeviceState::res
 hipError_t launch_persist_empty(const DeviceState& d, const PersistGeom& g, bool fp32,
                                 hipStream_t st);  // once, before the first solve
+template <typename T>  // a session's entry of the batched launch
+SweepArgs<T> persist_args(const DeviceState& d, T* x, int nprev_first, bool zero_x);
 size_t persist_lds_bytes(const PersistGeom& g, bool fp32);
 bool persist_batched(const PersistGeom& g);  // whether the batched launch has its class
 int persist_resident(const PersistGeom& g, bool fp32, bool batch, int cus);
