@@ -99,9 +99,11 @@ static MgTile make_tile(int N, int R, int cx, int wide, int hz) {
 // grid takes long chunks and a small one as many workgroups as it can fill.
 // Down / up of 256^3 from an FP64 residual, FP32: 40 / 43 us with 8 rows of 64
 // pairs by 32 planes; 42 / 58 with whole rows by 16 planes (two pairs a
-// thread), 49 / 47 with 16 whole rows (three), 54 / 57 with 16 planes.
+// thread), 49 / 47 with 16 whole rows (three), 54 / 57 with 16 planes. 128^3 9.2 /
+// 11.1 with 8 rows by 8 planes, 12.7 / 16.8 by 16, 10.5 / 12.4 with 4 rows; 64^3
+// 5.4 / 5.4 with 4 rows by 2 planes, 5.5 / 6.2 by 4.
 static MgTile mg_tile(int N) {
-  const int R = N >= 96 ? 8 : 4, cx = N >= 192 ? 32 : N >= 96 ? 8 : 4;
+  const int R = N >= 96 ? 8 : 4, cx = N >= 192 ? 32 : N >= 96 ? 8 : 2;
   return make_tile(N, R, cx, 64, 2);
 }
 
