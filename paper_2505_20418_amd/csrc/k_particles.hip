@@ -767,13 +767,27 @@ __global__ __launch_bounds__(kThreads) void k_finalize(int mode, int count, long
                                                        double* hist, int hist_cap) {
   __shared__ double red[8];
   auto slot = [&](int s) { return part + (size_t)s * pstride; };
+  // The step's first inner solve decided on the device, as the host decides
+  // the later ones: converged already if the true residual of the
+  // right-hand side meets thr, else an inner tolerance of
+  // max(reduction * residual, margin * thr).
+  auto inner_first = [&](double thr, double res, double reduction, double margin) {
+    ctl_st(&sc->thr_outer, thr);
+    if (res <= thr) {
+      ctl_st(&sc->done, 4);
+    } else {
+      const double a = reduction * res, b = margin * thr;
+      ctl_st(&sc->thr, (a < b) ? b : a);
+      ctl_st(&sc->done, 0);
+    }
+  };
   if (mode == FIN_QSUM) {
     const double s = sum_partials(slot(SL_QSUM), count, red);
     if (threadIdx.x == 0) {
       ctl_st(&sc->qsum, s);
       ctl_st(&sc->qbar, s / (double)G);
     }
-  } else if (mode == FIN_SOLVE_START) {
+  } else if (mode == FIN_SOLVE_START || mode == FIN_SOLVE_INNER) {
     const double qq = sum_partials(slot(SL_QQ), count, red);
     const double pp = sum_partials(slot(SL_PHIP), count, red);
     const double trr = sum_partials(slot(SL_TRR), count, red);
@@ -791,6 +805,9 @@ __global__ __launch_bounds__(kThreads) void k_finalize(int mode, int count, long
       ctl_st(&sc->pend, 0);
       ctl_st(&sc->done, 0);
       ctl_st(&sc->iters, 0);
+      if (mode == FIN_SOLVE_INNER)
+        inner_first((norm == MAZE_NORM_ABSMAX) ? tol : tol * sqrt(qq),
+                    (norm == MAZE_NORM_ABSMAX) ? tmx : sqrt(trr), param, coulomb_k);
     }
   } else if (mode == FIN_SOLVE_END) {
     const double xs = sum_partials(slot(SL_XSUM), count, red);
@@ -809,28 +826,16 @@ __global__ __launch_bounds__(kThreads) void k_finalize(int mode, int count, long
       if (energy_out) *energy_out = 0.5 * coulomb_k * e;
     }
   } else if (mode == FIN_INNER_FIRST) {
-    // The step's first inner solve decided on the device, as the host decides
-    // the later ones: converged already if the true residual of the
-    // right-hand side meets thr, else an inner tolerance of
-    // max(tol * residual, param * thr) (tol, param: the reduction and margin
-    // of the mixed refinement).
     if (threadIdx.x == 0) {
       const double thr = ctl_ld(&sc->thr);
       const double res = (ctl_ld(&sc->norm) == MAZE_NORM_ABSMAX) ? ctl_ld(&sc->true_max)
                                                                  : sqrt(ctl_ld(&sc->true_rr));
-      ctl_st(&sc->thr_outer, thr);
       ctl_st(&sc->max_iter, imax);
       ctl_st(&sc->itp[0], 0);
       ctl_st(&sc->itp[1], 0);
       ctl_st(&sc->pend, 0);
       ctl_st(&sc->iters, 0);
-      if (res <= thr) {
-        ctl_st(&sc->done, 4);
-      } else {
-        const double a = tol * res, b = param * thr;
-        ctl_st(&sc->thr, (a < b) ? b : a);
-        ctl_st(&sc->done, 0);
-      }
+      inner_first(thr, res, tol, param);
     }
   } else if (mode == FIN_INNER_END) {
     // The end of the step's first inner solve, decided as the host decides

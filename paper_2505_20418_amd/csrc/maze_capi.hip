@@ -1636,16 +1636,19 @@ static int step_one(maze_session* s, const double* pos, double* field, double* f
   }
   const bool mixed = s->cfg.precision == MAZE_MIXED;
   int rc = assign(s, pos);
-  if (rc == MAZE_OK) rc = step_rhs(s);
+  if (rc == MAZE_OK && !mixed) rc = step_rhs(s);
   if (rc != MAZE_OK) return rc;
+  if (mixed) {
+    HIP_TRY(launch_rhs_maze(d, s->geom, true, s->stream));
+    HIP_TRY(launch_finalize(d, FIN_SOLVE_INNER, s->geom.nwg, s->cfg.tol, kInnerReduction,
+                            kInnerMargin, nullptr, s->cfg.max_iter, s->cfg.residual_norm,
+                            s->stream));
+  }
   s->iters = 0;
   s->refinements = 0;
   s->converged = 0;
   s->trace_rows.clear();
   s->trace_pass = 0;
-  if (mixed)
-    HIP_TRY(launch_finalize(d, FIN_INNER_FIRST, 0, kInnerReduction, kInnerMargin, 0.0, nullptr,
-                            s->cfg.max_iter, s->cfg.residual_norm, s->stream));
   std::vector<Scalars> h;
   if (s->device < 0 || s->device >= 64) return MAZE_E_DEVICE;
   {

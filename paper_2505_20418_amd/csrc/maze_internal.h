@@ -237,6 +237,8 @@ constexpr int kInlineQsum = 1024;
 enum FinalizeMode : int {
   FIN_QSUM = 0,      // qsum, qbar from SL_QSUM over `count` partials
   FIN_SOLVE_START,   // qnorm, thr, pbar; resets it/done/iters
+  FIN_SOLVE_INNER,   // FIN_SOLVE_START, then FIN_INNER_FIRST (reduction and margin in
+                     // `param` and `coulomb_k`)
   FIN_SOLVE_END,     // xbar (from SL_XSUM), true residual
   FIN_ENERGY,        // energy from SL_ENERGY, writes energy_out
   FIN_INNER_END,     // FIN_SOLVE_END of a first inner solve; err = kErrMore if not the last
