@@ -205,7 +205,7 @@ static int part_stride_for(const DeviceState& d, const MarchGeom& g, const Sweep
 // fit on the chip, with or without MAZE_FLAG_SSTEP (the iterates are the same
 // in exact arithmetic, and a resident iteration moves no vectors that the
 // two-iteration form could spare: 128^3 FP64 MD step 5.20 ms launched in that
-// form, 2.6 resident). MAZE_PERSIST=0 in the environment keeps to launched
+// form, 2.26 resident). MAZE_PERSIST=0 in the environment keeps to launched
 // kernels.
 static PersistGeom persist_geom(const maze_config* c, int N) {
   const char* e = std::getenv("MAZE_PERSIST");
@@ -797,14 +797,17 @@ static hipError_t gate_enter(PersistGate& g, hipStream_t st) {
 }
 
 // Whether a session's next solve runs in the resident form (timed sweeps are
-// launched ones).
-static bool persist_of(const maze_session* s) { return s->pgeom.nwg > 0 && !s->prof; }
+// launched ones; g_gate has a place for each of the first 64 devices).
+static bool persist_of(const maze_session* s) {
+  return s->pgeom.nwg > 0 && !s->prof && s->device >= 0 && s->device < 64;
+}
 
 // Whether the resident solves of `ss` together take less time than one
 // batched solve of them by launched sweeps. Resident solves run (nearly) one
 // after the other, each at the latency of its exchange; a batched sweep moves
 // every session's bytes at the copy rate, with some 12 us per launch and class
-// as its floor. Iteration counts grow as N. Measured: 16 sessions of 32^3 to
+// as its floor. Iteration counts grow as N. Measured, with longer kernels around
+// the solves than now (10.9 and 31.2 ms): 16 sessions of 32^3 to
 // 128^3, half FP64, 13.6 ms against 24.2 ms launched; 64 mixed replicas of
 // 32^3 to 96^3 51.0 ms against 34.9 ms, so the line lies between; the
 // estimates of the two cases are 7.2 against 13.5 and 23 against 14.5.
