@@ -17,6 +17,7 @@
 
 #include "device_util.h"
 #include "philox.h"
+#include "rdf_plan.h"
 
 namespace maze {
 
@@ -249,6 +250,13 @@ __global__ __launch_bounds__(kRdfThreads, 8) void k_rdf(const double* __restrict
       }
     __syncthreads();
   };
+  // Counts a block, with the counters flushed before one could run over (every
+  // thread of the workgroup calls).
+  RdfTaken taken;
+  auto count = [&](bool flip, int ni, int nj) {
+    if (taken.flush_before(ni, nj)) flush();
+    count_block(s, q, flip, ni, nj);
+  };
   bool far = false;
   auto ion_at = [&](int i, double x, double y, double z) {
     RdfIon a;
@@ -321,7 +329,7 @@ __global__ __launch_bounds__(kRdfThreads, 8) void k_rdf(const double* __restrict
           });
           // fewer than kRdfThreads are left over, so the next step's fit
           if (nj >= kRdfThreads || base + kRdfThreads >= n) {
-            count_block(s, q, false, here, nj);
+            count(false, here, nj);
             nj = 0;
             __syncthreads();
           }
@@ -337,7 +345,6 @@ __global__ __launch_bounds__(kRdfThreads, 8) void k_rdf(const double* __restrict
     q.any_far = true;  // cheap beside all pairs
     const int wide = rdf_long(n);
     const long long nbi = (n + wide - 1) / wide, nbj = (n + kRdfBlockJ - 1) / kRdfBlockJ;
-    int done = 0;
     for (long long b = blockIdx.x; b < nbi * nbj; b += gridDim.x) {
       // the long side (`wide` ions from i0 on) takes the place of
       // j, the short one that of i
@@ -354,11 +361,7 @@ __global__ __launch_bounds__(kRdfThreads, 8) void k_rdf(const double* __restrict
         s.I[tid].n += species[j0 + tid] ? 1 : 0;
       }
       __syncthreads();
-      count_block(s, q, true, nj, ni);
-      if (++done == 1 << 17) {  // before a 32-bit counter could run over
-        done = 0;
-        flush();
-      }
+      count(true, nj, ni);
     }
   }
   flush();
