@@ -158,15 +158,11 @@ __device__ __forceinline__ void count_block(const RdfLds& s, const RdfJob& q, bo
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int* queue = s.queue + w * kRdfQueue;
   int have = 0;
-  // a wavefront takes 64 j ions at a time; where these are fewer than the
-  // wavefronts, each takes a share of the i ions
-  const int jw = (nj + 63) / 64, split = max(1, kRdfWaves / jw);
-  if (w >= jw * split) return;
-  const int i0 = ni * (w / jw) / split, i1 = ni * (w / jw + 1) / split;
-  for (int j0 = (w % jw) * 64; j0 < nj; j0 += (split > 1 ? nj : kRdfThreads)) {
+  const RdfShare t = rdf_share(ni, nj, w, kRdfWaves);
+  for (int j0 = t.j0; j0 < nj; j0 += kRdfThreads) {
     const int j = j0 + lane;
     const RdfIon b = s.J[min(j, nj - 1)];
-    for (int i = split > 1 ? i0 : 0; i < (split > 1 ? i1 : ni); ++i) {
+    for (int i = t.i0; i < t.i1; ++i) {
       const RdfIon a = s.I[i];
       const float dx = (float)(int)(b.x - a.x), dy = (float)(int)(b.y - a.y),
                   dz = (float)(int)(b.z - a.z);

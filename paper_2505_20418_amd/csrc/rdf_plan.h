@@ -25,4 +25,18 @@ struct RdfTaken {
   }
 };
 
+// Share of wavefront w in a block of ni by nj pairs: 64 j ions at a time,
+// from j0 on in steps of 64 * waves, with the i ions [i0, i1) each. Where the
+// j ions are fewer than 64 a wavefront, each takes a share of the i ions; a
+// wavefront without a share, and every one of an empty block, has j0 = nj.
+struct RdfShare {
+  int j0, i0, i1;
+};
+RDF_FN RdfShare rdf_share(int ni, int nj, int w, int waves) {
+  if (ni <= 0 || nj <= 0) return {nj, 0, 0};
+  const int jw = (nj + 63) / 64, split = waves / jw > 1 ? waves / jw : 1;
+  if (w >= jw * split) return {nj, 0, 0};
+  return {(w % jw) * 64, ni * (w / jw) / split, ni * (w / jw + 1) / split};
+}
+
 }  // namespace maze

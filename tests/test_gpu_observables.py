@@ -139,3 +139,35 @@ def test_pair_counts_by_cells_and_all_pairs(obs, n_cells, kind, r_frac):
         b = torch.searchsorted(e, r2[i, j], right=True) - 1
         want += torch.bincount((sp[a + i] + sp[j]) * 150 + b, minlength=450)
     assert torch.equal(h.hist, want)
+
+
+def all_pair_counts(h, p, species, box):
+    """The histogram h.accumulate(p) adds, from every pair's squared distance."""
+    e, nb, n = h.edges2, h.nbins, p.shape[0]
+    want = torch.zeros(3 * nb, dtype=torch.int64, device="cuda")
+    idx = torch.arange(n, device="cuda")
+    for a in range(0, n, 512):
+        r2 = torch.zeros(min(512, n - a), n, dtype=torch.float64, device="cuda")
+        for d in range(3):
+            dx = p[None, :, d] - p[a:a + 512, d, None]
+            dx = dx - torch.round(dx / box) * box
+            r2 = r2 + dx * dx
+        ok = (idx[None, :] > idx[a:a + 512, None]) & (r2 >= e[0]) & (r2 < e[-1])
+        i, j = torch.nonzero(ok, as_tuple=True)
+        b = torch.searchsorted(e, r2[i, j], right=True) - 1
+        want += torch.bincount((species[a + i] + species[j]) * nb + b, minlength=3 * nb)
+    return want
+
+
+@pytest.mark.parametrize("axis", [0, 2])
+def test_pair_counts_of_ions_in_order_of_position(obs, axis):
+    """Ions listed along an axis, as a crystal builder lists them: a cell's
+    neighbours fill whole chunks of the list and its end holds none, so the
+    last block of a cell is empty."""
+    s = inputs.molten_nacl(13, seed=13)
+    order = np.argsort(np.mod(s.pos[:, axis], s.box), kind="stable")
+    pos, sp = dev(s.pos[order]), s.species[order]
+    h = obs.PairHistogram(dev(sp, torch.int32), s.box, 0.16 * s.box, 150)
+    print(f"case: pair counts in order of axis {axis}, n={s.n_ions}", flush=True)
+    h.accumulate(pos)
+    assert torch.equal(h.hist, all_pair_counts(h, pos, dev(sp, torch.int64), s.box))

@@ -1,5 +1,6 @@
 """Host arithmetic of the pair histogram kernel (csrc/rdf_plan.h), compiled
-for the CPU: the flush rule of its 32-bit counters."""
+for the CPU: the flush rule of its 32-bit counters and the split of a block of pairs
+over its wavefronts."""
 import os
 import shutil
 import subprocess
@@ -49,4 +50,27 @@ def test_no_counter_runs_over(tmp_path, ni, nj):
   }}
   CHECK(flushed + counter == total);
   CHECK(flushes >= total / 0x100000000ull);
+""")
+
+
+def test_shares_cover_each_pair_once(tmp_path):
+    """Empty blocks have no share (the last chunk of a cell's neighbours may
+    add none), and every pair of the others is in exactly one."""
+    run_cpp(tmp_path, """
+  const int waves = 16;
+  const int ns[] = {0, 1, 2, 15, 16, 17, 63, 64, 65, 100, 255, 256};
+  const int js[] = {0, 1, 63, 64, 65, 127, 128, 300, 511, 512, 513, 1000, 1023, 1024, 1025,
+                    2047, 2048};
+  for (int ni : ns)
+    for (int nj : js) {
+      std::vector<int> hit((size_t)ni * nj + 1, 0);
+      for (int w = 0; w < waves; ++w) {
+        const RdfShare t = rdf_share(ni, nj, w, waves);
+        CHECK(t.i0 >= 0 && t.i1 <= ni && t.j0 >= 0);
+        for (int j0 = t.j0; j0 < nj; j0 += 64 * waves)
+          for (int j = j0; j < j0 + 64 && j < nj; ++j)
+            for (int i = t.i0; i < t.i1; ++i) ++hit[(size_t)i * nj + j];
+      }
+      for (size_t k = 0; k < (size_t)ni * nj; ++k) CHECK(hit[k] == 1);
+    }
 """)
