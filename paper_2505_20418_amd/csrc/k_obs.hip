@@ -190,17 +190,19 @@ __device__ __forceinline__ void count_block(const RdfLds& s, const RdfJob& q, bo
 // than it: a workgroup takes cells in turn, gathers a cell's ions and those
 // of the 27 cells around it by scanning the positions (which stay in the
 // caches), and counts only pairs of these. Else, or if a position is not
-// finite or more than 1e6 boxes away (its cell would be uncertain), all
-// pairs, in blocks. The decision rests on the edges and the positions alone,
-// so every workgroup takes the same one. Counts are integers: exact in any
-// order.
+// finite or more than 1e6 boxes away (its cell would be uncertain), or if the
+// ions crowd into a few cells (rdf_cell_heavy: the workgroup of such a cell
+// would work alone), all pairs, in blocks. The decision rests on the edges and
+// the positions alone, so every workgroup takes the same one: the first scan
+// counts the ions of every cell. Counts are integers: exact in any order.
 // What bounds it: FP64 work. With all pairs tested in FP64 and a division per
 // axis, 32768 ions to 12 of 102 A took 1.26 ms (4.3e11 pairs/s), though 0.7%
 // of these pairs are in range. The 24-bit test of all pairs takes 0.54 ms; the
 // cells (512 here) leave 5% of them and two scans of the positions per cell:
-// 0.26 ms. At 13824 ions and 216 cells the scans cost more than they save
+// 0.27 ms. At 13824 ions and 216 cells the scans cost more than they save
 // (0.120 against 0.095 ms), so cells start at 16384 ions. 1728 ions: 203 us
-// before, 14 now.
+// before, 14 now. 32768 ions in a drop of a tenth of the box: 77 ms by cells,
+// 2.5 by all pairs (of 0.4 of the box 6.7 and 0.9).
 constexpr int kRdfCellsMin = 6, kRdfCellsMax = 16, kRdfIonsMin = 16384, kRdfBlockJ = 64;
 // Long side of a block of all pairs: many blocks for few ions, full workgroups
 // for many.
@@ -302,17 +304,54 @@ __global__ __launch_bounds__(kRdfThreads, 8) void k_rdf(const double* __restrict
     __syncthreads();
     return have + total;
   };
+  // Ions per cell, in the place of the j ions (the first scan has none).
+  static_assert(sizeof(RdfIon) * kRdfJ >= sizeof(int) * kRdfCellsMax * kRdfCellsMax * kRdfCellsMax,
+                "the cells' ions are counted in the place of the j ions");
+  int* const cells = reinterpret_cast<int*>(s.J);
+  const int ncells = nc * nc * nc;
+  auto tally = [&](const RdfIon& a) {
+    atomicAdd(&cells[(cell1(a.x) * nc + cell1(a.y)) * nc + cell1(a.z)], 1);
+  };
+  auto no_cells = [&]() {  // after the scan that tallied: whether all pairs are taken
+    __syncthreads();
+    // no cell is heavy unless one would be among 27 like itself
+    bool heavy = far;
+    for (int c = tid; c < ncells; c += kRdfThreads)
+      heavy = heavy || rdf_cell_heavy(cells[c], 27ll * cells[c], n);
+    if (!__syncthreads_or(heavy ? 1 : 0)) return false;
+    heavy = false;
+    for (int c = tid; c < ncells; c += kRdfThreads) {
+      const int x = c / (nc * nc), y = (c / nc) % nc, z = c % nc;
+      int near = 0;
+#pragma unroll 1
+      for (int k = 0; k < 27; ++k) {
+        const int a = x + k / 9 - 1, b = y + (k / 3) % 3 - 1, d = z + k % 3 - 1;
+        near += cells[((a < 0 ? nc - 1 : a == nc ? 0 : a) * nc +
+                       (b < 0 ? nc - 1 : b == nc ? 0 : b)) * nc +
+                      (d < 0 ? nc - 1 : d == nc ? 0 : d)];
+      }
+      heavy = heavy || rdf_cell_heavy(cells[c], near, n);
+    }
+    return __syncthreads_or(far || heavy ? 1 : 0) != 0;
+  };
+  if (ncells > 0) {
+    for (int c = tid; c < ncells; c += kRdfThreads) cells[c] = 0;
+    __syncthreads();
+  }
   if constexpr (CELLS) {
-    for (int c = blockIdx.x; c < nc * nc * nc; c += gridDim.x) {
+    bool first = true;
+    for (int c = blockIdx.x; c < ncells; c += gridDim.x) {
       const int cx = c / (nc * nc), cy = (c / nc) % nc, cz = c % nc;
       for (int from = 0;; from += kRdfI) {  // the cell's ions, kRdfI at a time
         int ni = 0;
         for (int base = 0; base < n; base += kRdfThreads)
           ni = append(base, ni, s.I, from, kRdfI, [&](const RdfIon& a) {
+            if (first) tally(a);
             return cell1(a.x) == cx && cell1(a.y) == cy && cell1(a.z) == cz;
           });
         // seen by every workgroup in its first scan: all pairs instead
-        if (__syncthreads_or(far ? 1 : 0)) return;
+        if (first && no_cells()) return;
+        first = false;
         const int here = min(ni - from, kRdfI);
         int nj = 0;
         for (int base = 0; here > 0 && base < n; base += kRdfThreads) {
@@ -334,9 +373,9 @@ __global__ __launch_bounds__(kRdfThreads, 8) void k_rdf(const double* __restrict
       }
     }
   } else {
-    if (nc > 0) {
-      for (int i = tid; i < n; i += kRdfThreads) (void)ion_of(i);
-      if (!__syncthreads_or(far ? 1 : 0)) return;
+    if (ncells > 0) {
+      for (int i = tid; i < n; i += kRdfThreads) tally(ion_of(i));
+      if (!no_cells()) return;
     }
     q.any_far = true;  // cheap beside all pairs
     const int wide = rdf_long(n);

@@ -39,4 +39,13 @@ RDF_FN RdfShare rdf_share(int ni, int nj, int w, int waves) {
   return {(w % jw) * 64, ni * (w / jw) / split, ni * (w / jw + 1) / split};
 }
 
+// Whether a cell of `here` ions with `near` ions in it and around it makes the
+// cell form slower than all pairs. A cell is one workgroup's; with all pairs
+// a workgroup (of the 512 that are resident) has n^2 / 1024 to test. Cells of
+// even density on the coarsest division, six a side, have 0.6 of that.
+RDF_FN bool rdf_cell_heavy(long long here, long long near, int n) {
+  return (unsigned long long)here * (unsigned long long)near >
+         (unsigned long long)n * (unsigned long long)n / 1024;
+}
+
 }  // namespace maze

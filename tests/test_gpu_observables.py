@@ -171,3 +171,30 @@ def test_pair_counts_of_ions_in_order_of_position(obs, axis):
     print(f"case: pair counts in order of axis {axis}, n={s.n_ions}", flush=True)
     h.accumulate(pos)
     assert torch.equal(h.hist, all_pair_counts(h, pos, dev(sp, torch.int64), s.box))
+
+
+@pytest.mark.parametrize("shrink", [0.4, 0.1])
+def test_pair_counts_of_a_crowded_frame(obs, shrink):
+    """Ions in a drop: a few cells hold them all, and a workgroup a cell would
+    leave the device idle. The counts are those of every pair, and the frame
+    takes no more than 20 times an even one of as many ions (its all-pairs form
+    tests 20 times the pairs that the cells of the even frame leave)."""
+    s = inputs.molten_nacl(13, seed=14)
+    pos = 0.5 * s.box + (np.mod(s.pos, s.box) - 0.5 * s.box) * shrink
+    h = obs.PairHistogram(dev(s.species, torch.int32), s.box, 0.16 * s.box, 150)
+    print(f"case: pair counts of a drop of {shrink} of the box, n={s.n_ions}", flush=True)
+    drop, even = dev(pos), dev(s.pos)
+    h.accumulate(drop)
+    assert torch.equal(h.hist, all_pair_counts(h, drop, dev(s.species, torch.int64), s.box))
+
+    def ms(p):
+        best = float("inf")
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            h.accumulate(p)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+    assert ms(drop) <= 20.0 * ms(even)

@@ -74,3 +74,19 @@ def test_shares_cover_each_pair_once(tmp_path):
       for (size_t k = 0; k < (size_t)ni * nj; ++k) CHECK(hit[k] == 1);
     }
 """)
+
+
+def test_cells_for_even_frames_only(tmp_path):
+    """Even density is never heavy, with room for a third more ions than the mean in a
+    cell; all ions in one cell, or in the cells of a plane, are."""
+    run_cpp(tmp_path, """
+  for (int n : {16384, 17576, 32768, 100000, 3000000})
+    for (int nc = 6; nc <= 16; ++nc) {
+      const long long mean = n / (nc * nc * nc);
+      CHECK(!rdf_cell_heavy(mean, 27 * mean, n));
+      CHECK(!rdf_cell_heavy(4 * mean / 3, 27 * mean, n));
+      CHECK(rdf_cell_heavy(n, n, n));
+      const long long plane = n / (nc * nc);
+      CHECK(rdf_cell_heavy(plane, 9 * plane, n) == (9 * 1024 > nc * nc * nc * nc));
+    }
+""")
