@@ -162,7 +162,7 @@ size_t maze_device_bytes(const maze_config* cfg);
 int maze_init(const maze_config* cfg, const double* charges_dev,
               const double* pos0_dev, maze_session** out, maze_stats* st);
 
-/* Resident solves. On grids up to 128^3 the Jacobi PLCG (with or without
+/* Resident solves (maze_resident_solves counts them). On grids up to 128^3 the Jacobi PLCG (with or without
  * MAZE_FLAG_SSTEP) runs all iterations of a solve in one launch whose
  * workgroups keep x, r, p and A p on the chip and exchange boundary rows and
  * sums (same per-point arithmetic as the launched sweeps; the sums' order,
@@ -317,6 +317,12 @@ int maze_basis_shape(const maze_session* s, int32_t* out4);
  * per thread is N / 64. MAZE_BASIS_SHAPE="zv:W:cx" (cx planes per x run)
  * forces one. */
 int maze_sstep_layout(const maze_session* s, int32_t* out2);
+
+/* Resident solves of a session (see maze_step). out3 (HOST, 3 int64): 1 if
+ * its next solve alone is a resident one, else 0; the resident solves run to
+ * their end so far; the resident solves that gave up waiting and were
+ * repeated by launched sweeps. */
+int maze_resident_solves(const maze_session* s, int64_t* out3);
 
 /* Residual trace of the last solve (for convergence studies such as the
  * residual-versus-iteration comparison of Appendix B). When enabled, each

@@ -54,6 +54,7 @@ struct maze_session {
   SweepGeom sbasis{};    // basis kernel of the two-iteration CG (own shape)
   PersistGeom pgeom{};   // resident solves; nwg = 0: solved by launched sweeps
   int president = 0;     // workgroups of a batched resident launch that fit the device
+  long long resident_solves = 0, resident_lost = 0;  // run to their end, given up
   hipStream_t stream = nullptr;
   // captured chunks of kPollBatch sweeps, [fp32][parity of the first sweep]
   // [slot]: a graph holds its kernels' arguments, and the solution vector
@@ -917,6 +918,7 @@ static int run_persist(std::vector<CgJob>& jobs, bool fp32, bool zero_x) {
     jobs[i].err = h[i].err;
     jobs[i].iters = h[i].iters;
     jobs[i].code = h[i].done ? h[i].done : 3;
+    if (h[i].err != kErrAborted) ss[i]->resident_solves += 1;
     if (!jobs[i].err && ss[i]->trace) {
       const int rc = trace_collect(ss[i], jobs[i].iters, h[i].qnorm);
       if (rc != MAZE_OK) return rc;
@@ -1243,6 +1245,7 @@ static int solve_error(int err) { return err == kErrAborted ? kRepeat : MAZE_E_N
 // Makes a session whose resident solve gave up ready for its repetition:
 // launched sweeps from here on, the error flag cleared.
 static int persist_off(maze_session* s) {
+  s->resident_lost += 1;
   s->pgeom.nwg = 0;
   HIP_TRY(hipStreamSynchronize(s->stream));
   HIP_TRY(hipMemsetAsync(&s->d.sc->err, 0, sizeof(int32_t), s->stream));
@@ -1674,6 +1677,7 @@ static int step_one(maze_session* s, const double* pos, double* field, double* f
   }
   Scalars& v = h[0];
   const int err = v.err;
+  if (err != kErrAborted) s->resident_solves += 1;
   if (mixed && (!err || err == kErrMore) && v.done != 4) {
     s->refinements = 1;
     s->last_inner[0] = v.iters;
@@ -2518,6 +2522,7 @@ int batch_process(maze_batch* b, const maze_batch::Poll& P) {
       }
       const int code = h.done ? h.done : 3;
       b->dirty = true;
+      if (j.res) s->resident_solves += 1;
       if (!j.fp32) {
         s->iters = h.iters;
         s->converged = (code == 1);
@@ -3020,6 +3025,14 @@ int maze_launch_shape(const maze_session* s, int32_t* out8) {
     out8[4 * i + 2] = g[i]->nwg;
     out8[4 * i + 3] = g[i]->S;
   }
+  return MAZE_OK;
+}
+
+int maze_resident_solves(const maze_session* s, int64_t* out3) {
+  if (!s || !out3) return MAZE_E_INVALID;
+  out3[0] = persist_of(s) ? 1 : 0;
+  out3[1] = s->resident_solves;
+  out3[2] = s->resident_lost;
   return MAZE_OK;
 }
 

@@ -180,3 +180,44 @@ def test_queued_ahead_step_with_bad_positions_changes_nothing(maze):
     run.step()
     assert torch.isfinite(run.f_es).all() and torch.isfinite(run.scalars).all()
     run.close()
+
+
+@pytest.mark.parametrize("prec,tol", [(0, 1e-10), (1, 1e-7)])
+def test_given_up_solves_are_counted(maze, monkeypatch, prec, tol):
+    """What a session reports of its solves, alone, in a batch and in a
+    continuous batch: each was given up with no polls allowed, and none was
+    with the polls there usually are."""
+    N = 32
+    for spin in (None, "0"):
+        print(f"case: solves given up are counted, precision {prec}, spin {spin}", flush=True)
+        monkeypatch.delenv("MAZE_PERSIST_SPIN", raising=False)
+        s, alone = make(maze, N, prec, tol, 12)
+        _, a = make(maze, N, prec, tol, 12)
+        _, b = make(maze, N, prec, tol, 12)
+        _, flight = make(maze, N, prec, tol, 12)
+        p = dev(s.pos + s.vel)
+        before = [maze.maze_resident_solves(x.handle) for x in (alone, a, b, flight)]
+        assert all(x["resident"] and x["given_up"] == 0 for x in before)
+        if spin is not None:
+            monkeypatch.setenv("MAZE_PERSIST_SPIN", spin)
+        assert alone.step(p)["status"] == 0
+        assert maze.maze_step_batch([a.handle, b.handle], [p, p])[0] == 0
+        batch = maze.Batch(max_sessions=4)
+        batch.add(flight.handle, p, tag=1)
+        done = []
+        for _ in range(100000):
+            batch.advance()
+            done += batch.take()
+            if done:
+                break
+        assert done[0][1]["status"] == 0
+        for x, old in zip((alone, a, b, flight), before):
+            now = maze.maze_resident_solves(x.handle)
+            if spin is None:
+                assert now["given_up"] == 0 and now["solves"] > old["solves"]
+            else:
+                assert now["given_up"] == 1 and now["solves"] == old["solves"]
+                assert not now["resident"]
+        batch.close()
+        for x in (alone, a, b, flight):
+            x.close()
