@@ -3,6 +3,9 @@
 // device convergence flag, the mixed-precision refinement loop, checkpoints
 // and the MD driver entry points.
 #include <algorithm>
+#include <atomic>
+#include <chrono>
+#include <condition_variable>
 #include <cstdlib>
 #include <map>
 #include <mutex>
@@ -13,6 +16,7 @@
 #include <vector>
 
 #include "maze_internal.h"
+#include "resident_gate.h"
 
 using namespace maze;
 
@@ -54,6 +58,7 @@ struct maze_session {
   SweepGeom sbasis{};    // basis kernel of the two-iteration CG (own shape)
   PersistGeom pgeom{};   // resident solves; nwg = 0: solved by launched sweeps
   int president = 0;     // workgroups of a batched resident launch that fit the device
+  int pneed = 0, pcap = 0;  // of a resident solve at the gate
   long long resident_solves = 0, resident_lost = 0;  // run to their end, given up
   hipStream_t stream = nullptr;
   // captured chunks of kPollBatch sweeps, [fp32][parity of the first sweep]
@@ -769,20 +774,151 @@ static int batch_loop(std::vector<CgJob>& jobs, const std::vector<int>& order, B
 static int run_sstep_batch(std::vector<CgJob>& jobs, bool fp32, bool zero_x, int first_batch);
 
 // ---- resident solves -----------------------------------------------------------
-// The workgroups of a resident solve wait for each other, so two of them must
-// not share a device half started. The launches of one process are kept
-// apart: a call that waits for its solve holds the device's gate until the
-// solve has ended, and a continuous batch, which does not wait, leaves an
-// event that launches on other streams wait for. Another process's kernels
-// can still delay a solve past its bounded waits: it then ends as kErrAborted
-// and is repeated by launched sweeps.
+// The workgroups of a resident solve wait for each other, so solves that
+// could keep each other from becoming resident must not meet on a device. A
+// device's gate knows the solves of this process that have not ended
+// (resident_gate.h); a new one is queued behind the end of those it does not
+// fit beside, on the device: the host holds the gate only while it queues.
+// Another process's kernels can still delay a solve past its bounded waits:
+// it then ends as kErrAborted and is repeated by launched sweeps.
 struct PersistGate {
   std::mutex mu;
-  hipEvent_t ev = nullptr;       // the last solve nobody has waited for
-  hipStream_t stream = nullptr;  // its stream
-  bool pending = false;
+  std::condition_variable ends;  // a call has seen its solve end
+  GateLedger led;
+  hipStream_t stream[GateLedger::kMax] = {nullptr};
+  hipEvent_t ev[GateLedger::kMax] = {nullptr};  // the solve's end, once recorded
+  bool recorded[GateLedger::kMax] = {false};
+  bool ready = false, used = false;
+  hipStream_t last = nullptr;
+  std::atomic<bool> shared{false};  // solves have come on more than one stream
 };
 static PersistGate g_gate[64];
+
+static bool gate_setup(int device) {
+  if (device < 0 || device >= 64) return false;
+  PersistGate& g = g_gate[device];
+  std::lock_guard<std::mutex> lk(g.mu);
+  if (g.ready) return true;
+  for (hipEvent_t& e : g.ev)
+    if (!e && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
+      (void)hipGetLastError();
+      e = nullptr;
+      return false;
+    }
+  g.ready = true;
+  return true;
+}
+
+// A call's solves at the gate. Holds the gate from enter to queued or leave.
+// The end of a solve is recorded on its stream only if another stream has to
+// wait for it while the call is still there, or where the call does not wait
+// (leave) or fails.
+class PersistTurn {
+ public:
+  PersistTurn() = default;
+  PersistTurn(const PersistTurn&) = delete;
+  PersistTurn& operator=(const PersistTurn&) = delete;
+  ~PersistTurn() {
+    if (slot_ < 0) return;
+    if (!lk_.owns_lock()) lk_.lock();
+    (void)leave();
+  }
+
+  // host: the call may wait for its turn on the host.
+  hipError_t enter(int device, hipStream_t st, int need, int cap, bool host) {
+    PersistGate& g = g_gate[device];
+    g_ = &g;
+    lk_ = std::unique_lock<std::mutex>(g.mu);
+    if (g.used && g.last != st) g.shared = true;
+    g.used = true;
+    g.last = st;
+    // the per-thread stream is another one in each thread
+    const uint64_t lane = st == hipStreamPerThread ? ~(uint64_t)g.led.last
+                                                   : (uint64_t)(uintptr_t)st;
+    uint32_t behind = 0;
+    for (;;) {
+      for (int i = 0; i < GateLedger::kMax; ++i)
+        if (g.led.at[i].id && g.recorded[i]) {
+          if (hipEventQuery(g.ev[i]) == hipSuccess) g.led.remove(i, g.led.at[i].id);
+          else (void)hipGetLastError();
+        }
+      if (g.led.free_place() < 0) {
+        const int o = g.led.oldest();
+        hipError_t e = record(o);
+        if (e == hipSuccess) e = hipEventSynchronize(g.ev[o]);
+        if (e != hipSuccess) return e;
+        g.led.remove(o, g.led.at[o].id);
+      }
+      behind = g.led.waits(lane, need, cap);
+      if (!host || !behind || !g.led.waiting()) break;
+      // a solve of a continuous batch ends without a call to tell
+      g.ends.wait_for(lk_, std::chrono::microseconds(200));
+    }
+    for (int i = 0; i < GateLedger::kMax; ++i) {
+      if (!(behind >> i & 1)) continue;
+      hipError_t e = record(i);
+      if (e == hipSuccess) e = hipStreamWaitEvent(st, g.ev[i], 0);
+      if (e != hipSuccess) return e;
+    }
+    slot_ = g.led.free_place();
+    id_ = g.led.add(slot_, lane, need, cap, behind);
+    g.stream[slot_] = st;
+    g.recorded[slot_] = false;
+    return hipSuccess;
+  }
+  // The solve has been queued; the call will wait for it.
+  void queued() {
+    if (g_->stream[slot_] == hipStreamPerThread) (void)record(slot_);
+    lk_.unlock();
+  }
+  // The call has waited for the solve.
+  void ended() {
+    lk_.lock();
+    g_->led.remove(slot_, id_);
+    slot_ = -1;
+    lk_.unlock();
+    g_->ends.notify_all();
+  }
+  // The solve has been queued and is not waited for.
+  hipError_t leave() {
+    hipError_t e = hipSuccess;
+    if (g_->led.holds(slot_, id_) && (e = record(slot_)) != hipSuccess) {
+      (void)hipGetLastError();  // nobody could wait for it later
+      e = hipStreamSynchronize(g_->stream[slot_]);
+      g_->led.remove(slot_, id_);
+    }
+    slot_ = -1;
+    lk_.unlock();
+    return e;
+  }
+
+ private:
+  hipError_t record(int i) {
+    if (g_->recorded[i]) return hipSuccess;
+    const hipError_t e = hipEventRecord(g_->ev[i], g_->stream[i]);
+    g_->recorded[i] = e == hipSuccess;
+    return e;
+  }
+  PersistGate* g_ = nullptr;
+  int slot_ = -1;
+  long long id_ = 0;
+  std::unique_lock<std::mutex> lk_;
+};
+
+// Where several streams solve on the device, a call whose stream still has
+// work of the caller's queued (asked as it begins) waits for that before it
+// enters, so that other streams wait for its solve alone.
+static bool gate_shared(int device) { return device >= 0 && device < 64 && g_gate[device].shared; }
+static bool gate_late(const maze_session* s) {
+  if (!gate_shared(s->device) || hipStreamQuery(s->stream) == hipSuccess) return false;
+  (void)hipGetLastError();  // hipErrorNotReady
+  return true;
+}
+static int gate_drain(maze_session* s) {
+  HIP_TRY(hipEventRecord(s->ev[0], s->stream));
+  HIP_TRY(hipEventSynchronize(s->ev[0]));
+  return MAZE_OK;
+}
 
 // Polls after which a workgroup gives up (about 1 us each).
 // MAZE_PERSIST_SPIN in the environment sets it (0: every solve is repeated
@@ -790,11 +926,6 @@ static PersistGate g_gate[64];
 static unsigned persist_spin() {
   const char* e = std::getenv("MAZE_PERSIST_SPIN");
   return e ? (unsigned)std::strtoul(e, nullptr, 10) : 1u << 21;
-}
-
-static hipError_t gate_enter(PersistGate& g, hipStream_t st) {
-  if (!g.pending || g.stream == st) return hipSuccess;
-  return hipStreamWaitEvent(st, g.ev, 0);
 }
 
 // Whether a session's next solve runs in the resident form (timed sweeps are
@@ -889,6 +1020,17 @@ static int queue_persist(const std::vector<int>& idx, F job, bool fp32, bool zer
 }
 static_assert(sizeof(PersistGeom) <= sizeof(SweepGeom), "the batch table's geometry array");
 
+// Enters the gate with the solves of `ss`, which may run side by side.
+static hipError_t persist_enter(PersistTurn& turn, int device, hipStream_t st,
+                                const std::vector<maze_session*>& ss, bool host) {
+  int need = 0, cap = ss[0]->pcap;
+  for (const maze_session* s : ss) {
+    need += s->pneed;
+    cap = std::min(cap, s->pcap);
+  }
+  return turn.enter(device, st, need, cap, host);
+}
+
 // Runs the jobs' solves in the resident form and waits for them. A solve
 // that gave up waiting comes back with err = kErrAborted.
 static int run_persist(std::vector<CgJob>& jobs, bool fp32, bool zero_x) {
@@ -906,14 +1048,18 @@ static int run_persist(std::vector<CgJob>& jobs, bool fp32, bool zero_x) {
   std::vector<maze_session*> ss(n);
   for (int i = 0; i < n; ++i) ss[i] = jobs[i].s;
   std::vector<Scalars> h;
-  {
-    PersistGate& g = g_gate[device];
-    std::lock_guard<std::mutex> lk(g.mu);
-    HIP_TRY(gate_enter(g, st));
-    int rc = queue_persist(idx, [&](int i) -> const CgJob& { return jobs[i]; }, fp32, zero_x, t, st);
-    if (rc == MAZE_OK) rc = gather_scalars(ss, h);
+  if (gate_shared(device)) {
+    const int rc = gate_drain(ss[0]);
     if (rc != MAZE_OK) return rc;
   }
+  PersistTurn turn;
+  HIP_TRY(persist_enter(turn, device, st, ss, true));
+  int rc = queue_persist(idx, [&](int i) -> const CgJob& { return jobs[i]; }, fp32, zero_x, t, st);
+  if (rc != MAZE_OK) return rc;
+  turn.queued();
+  rc = gather_scalars(ss, h);
+  if (rc != MAZE_OK) return rc;
+  turn.ended();
   for (int i = 0; i < n; ++i) {
     jobs[i].err = h[i].err;
     jobs[i].iters = h[i].iters;
@@ -1624,9 +1770,11 @@ static int step_tail(maze_session* s, double* field, double* forces, double* ene
 // 290 us against 280, 64^3 mixed MD step 341 against 327; 128^3 FP64 0.5 %
 // less). A step that turns out to need more (an
 // inner solve after the first, the launched kernels) has Scalars::err set on the
-// device, its tail does nothing, and the rest is done step by step.
+// device, its tail does nothing, and the rest is done step by step. late: what
+// gate_late said before the call queued anything.
 static int step_one(maze_session* s, const double* pos, double* field, double* forces,
-                    double* energy, const maze_md_state* md, long long k, maze_stats* st) {
+                    double* energy, const maze_md_state* md, long long k, bool late,
+                    maze_stats* st) {
   DeviceState& d = s->d;
   std::vector<maze_session*> one{s};
   if (!persist_of(s) || s->trace || s->cfg.max_iter <= 0) {
@@ -1641,6 +1789,7 @@ static int step_one(maze_session* s, const double* pos, double* field, double* f
     return finish_call(s, st);
   }
   const bool mixed = s->cfg.precision == MAZE_MIXED;
+  if (s->device < 0 || s->device >= 64) return MAZE_E_DEVICE;
   int rc = assign(s, pos);
   if (rc == MAZE_OK && !mixed) rc = step_rhs(s);
   if (rc != MAZE_OK) return rc;
@@ -1656,25 +1805,27 @@ static int step_one(maze_session* s, const double* pos, double* field, double* f
   s->trace_rows.clear();
   s->trace_pass = 0;
   std::vector<Scalars> h;
-  if (s->device < 0 || s->device >= 64) return MAZE_E_DEVICE;
-  {
-    PersistGate& g = g_gate[s->device];
-    std::lock_guard<std::mutex> lk(g.mu);
-    HIP_TRY(gate_enter(g, s->stream));
-    HIP_TRY(launch_persist(d, s->pgeom, mixed ? (void*)d.e32 : (void*)d.y, mixed, mixed,
-                           s->geom.nwg, persist_spin(), s->stream));
-    if (mixed) {
-      HIP_TRY(launch_add_correction(d, d.y, s->stream));
-      HIP_TRY(launch_refine(d, s->geom, d.y, true, s->stream));
-    } else {
-      HIP_TRY(launch_true_residual(d, s->geom, d.y, s->stream));
-    }
-    HIP_TRY(launch_finalize(d, mixed ? FIN_INNER_END : FIN_SOLVE_END, s->geom.nwg, 0.0, 0.0, 0.0,
-                            nullptr, s->cfg.max_iter, 0, s->stream));
-    rc = step_tail(s, field, forces, energy, md, k);
-    if (rc == MAZE_OK) rc = gather_scalars(one, h);
+  if (late) {
+    rc = gate_drain(s);
     if (rc != MAZE_OK) return rc;
   }
+  PersistTurn turn;
+  HIP_TRY(persist_enter(turn, s->device, s->stream, one, true));
+  HIP_TRY(launch_persist(d, s->pgeom, mixed ? (void*)d.e32 : (void*)d.y, mixed, mixed,
+                         s->geom.nwg, persist_spin(), s->stream));
+  turn.queued();
+  if (mixed) {
+    HIP_TRY(launch_add_correction(d, d.y, s->stream));
+    HIP_TRY(launch_refine(d, s->geom, d.y, true, s->stream));
+  } else {
+    HIP_TRY(launch_true_residual(d, s->geom, d.y, s->stream));
+  }
+  HIP_TRY(launch_finalize(d, mixed ? FIN_INNER_END : FIN_SOLVE_END, s->geom.nwg, 0.0, 0.0, 0.0,
+                          nullptr, s->cfg.max_iter, 0, s->stream));
+  rc = step_tail(s, field, forces, energy, md, k);
+  if (rc == MAZE_OK) rc = gather_scalars(one, h);
+  if (rc != MAZE_OK) return rc;
+  turn.ended();
   Scalars& v = h[0];
   const int err = v.err;
   if (err != kErrAborted) s->resident_solves += 1;
@@ -2423,10 +2574,10 @@ int batch_queue_resident(maze_batch* b, bool* any) {
       if (idx.empty()) continue;
       if (*any) return MAZE_OK;  // one table per poll: the others' turn comes with the next
       *any = true;
-      PersistGate& g = g_gate[b->device];
-      std::lock_guard<std::mutex> lk(g.mu);
-      if (!g.ev) HIP_TRY(hipEventCreateWithFlags(&g.ev, hipEventDisableTiming));
-      HIP_TRY(gate_enter(g, b->stream));
+      std::vector<maze_session*> ss;
+      for (int i : idx) ss.push_back(b->jobs[i].s);
+      PersistTurn turn;
+      HIP_TRY(persist_enter(turn, b->device, b->stream, ss, false));
       b->rtab_cur ^= 1;
       const int rc = queue_persist(
           idx,
@@ -2438,9 +2589,7 @@ int batch_queue_resident(maze_batch* b, bool* any) {
           },
           f == 1, z == 1, &b->rtab[b->rtab_cur], b->stream);
       if (rc != MAZE_OK) return rc;
-      HIP_TRY(hipEventRecord(g.ev, b->stream));
-      g.stream = b->stream;
-      g.pending = true;
+      HIP_TRY(turn.leave());
       for (int i : idx) {
         b->jobs[i].res = 2;
         b->jobs[i].ready = b->polls;
@@ -2766,8 +2915,10 @@ int maze_init(const maze_config* cfg, const double* charges_dev, const double* p
     const int cus = device_cus();
     const bool batched = persist_batched(s->pgeom);
     s->president = batched ? persist_resident(s->pgeom, mixed, true, cus) : 0;
-    if ((batched && s->president < s->pgeom.nwg) ||
-        persist_resident(s->pgeom, mixed, false, cus) < s->pgeom.nwg)
+    const int alone = persist_resident(s->pgeom, mixed, false, cus);
+    s->pneed = gate_need(s->pgeom.nwg, cus);
+    s->pcap = cus > 0 ? gate_cap((batched ? std::min(alone, s->president) : alone) / cus) : 0;
+    if ((batched && s->president < s->pgeom.nwg) || alone < s->pgeom.nwg || !gate_setup(s->device))
       s->pgeom.nwg = 0;
   }
   s->sweep_tp = throughput_sweep(s->d, s->cfg.precision == MAZE_MIXED);
@@ -2833,7 +2984,7 @@ int maze_step(maze_session* s, const double* pos_dev, double* field_dev, double*
               double* energy_dev, maze_stats* st) {
   if (!s || !pos_dev) return MAZE_E_INVALID;
   hipSetDevice(s->device);
-  return step_one(s, pos_dev, field_dev, forces_dev, energy_dev, nullptr, 0, st);
+  return step_one(s, pos_dev, field_dev, forces_dev, energy_dev, nullptr, 0, gate_late(s), st);
 }
 
 int maze_solve(maze_session* s, int guess, const double* pos_dev, double* field_dev,
@@ -3096,8 +3247,9 @@ int maze_md_step(maze_session* s, const maze_md_state* md, maze_stats* st) {
   if (rc != MAZE_OK) return rc;
   hipSetDevice(s->device);
   const long long k = s->step;  // noise counter of the Langevin half steps
+  const bool late = gate_late(s);
   HIP_TRY(launch_md_kick_drift(*md, k, s->stream));
-  return step_one(s, md->pos_dev, nullptr, md->f_es_dev, md->scalars_dev + 6, md, k, st);
+  return step_one(s, md->pos_dev, nullptr, md->f_es_dev, md->scalars_dev + 6, md, k, late, st);
 }
 
 int maze_md_step_batch(maze_session* const* sessions, const maze_md_state* const* mds,

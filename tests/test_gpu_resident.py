@@ -221,3 +221,168 @@ def test_given_up_solves_are_counted(maze, monkeypatch, prec, tol):
         batch.close()
         for x in (alone, a, b, flight):
             x.close()
+
+
+# ---- several streams and threads -------------------------------------------------
+# grid, precision, tolerance: solves that share the device, and ones that need
+# it to themselves
+KINDS = [(32, 0, 1e-10), (32, 1, 1e-6), (48, 0, 1e-9), (64, 1, 1e-7), (100, 0, 1e-8)]
+
+
+def alone_fields(maze, kind, seed, steps):
+    """Fields of a session stepped with nothing else on the device."""
+    s, x = make(maze, *kind, seed)
+    out = []
+    for k in range(steps):
+        assert x.step(dev(s.pos + (k + 1) * s.vel))["status"] == 0
+        out.append(x.grid(maze.GRID_PHI).clone())
+    x.close()
+    torch.cuda.synchronize()
+    return out
+
+
+def on_stream(maze, kind, seed, stream):
+    with torch.cuda.stream(stream):
+        return make(maze, *kind, seed, stream=stream.cuda_stream)
+
+
+def kept_resident(maze, *sessions):
+    for x in sessions:
+        got = maze.maze_resident_solves(x.handle)
+        assert got["resident"] and got["given_up"] == 0, got
+
+
+def test_threads_with_streams_of_their_own(maze):
+    """A session a thread, each on its own stream: every step's field is the
+    one it gets alone, and no solve gives up."""
+    import threading
+    steps = 40
+    print(f"case: threads {KINDS}", flush=True)
+    want = [alone_fields(maze, k, 80 + i, steps) for i, k in enumerate(KINDS)]
+    made = [on_stream(maze, k, 80 + i, torch.cuda.Stream()) for i, k in enumerate(KINDS)]
+    pos = [[dev(s.pos + (k + 1) * s.vel) for k in range(steps)] for s, _ in made]
+    torch.cuda.synchronize()
+    got = [[] for _ in KINDS]
+    failed = []
+
+    def work(i):
+        try:
+            x = made[i][1]
+            for k in range(steps):
+                assert x.step(pos[i][k])["status"] == 0
+                got[i].append(x.grid(maze.GRID_PHI))
+        except BaseException as e:  # noqa: BLE001
+            failed.append((i, e))
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(len(KINDS))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert not failed, failed
+    kept_resident(maze, *(x for _, x in made))
+    for i in range(len(KINDS)):
+        for k in range(steps):
+            assert torch.equal(got[i][k], want[i][k]), (KINDS[i], k)
+    for _, x in made:
+        x.close()
+
+
+def test_continuous_batches_beside_steps_on_other_streams(maze):
+    """Two continuous batches, whose resident solves nobody waits for, and steps
+    of other sessions, on three streams: each result is the one alone."""
+    print(f"case: two batches and steps on three streams {KINDS}", flush=True)
+    want = [alone_fields(maze, k, 90 + i, 3) for i, k in enumerate(KINDS)]
+    s1, s2, s3 = (torch.cuda.Stream() for _ in range(3))
+    groups = [[on_stream(maze, k, 90 + i, st) for i, k in enumerate(KINDS)] for st in (s1, s2, s3)]
+    batches = [maze.Batch(max_sessions=8, stream=s1.cuda_stream),
+               maze.Batch(max_sessions=8, stream=s2.cuda_stream)]
+    for k in range(3):
+        left = [len(KINDS), len(KINDS)]
+        p = [dev(s.pos + (k + 1) * s.vel) for s, _ in groups[0]]
+        torch.cuda.synchronize()
+        for b, g in zip(batches, groups):
+            for i, (_, x) in enumerate(g):
+                b.add(x.handle, p[i], tag=i)
+        own = list(enumerate(groups[2]))
+        for _ in range(100000):
+            for j, b in enumerate(batches):
+                if left[j]:
+                    b.advance()
+                    for tag, st in b.take():
+                        assert st["status"] == 0
+                        left[j] -= 1
+            if own:
+                i, (_, x) = own.pop()
+                assert x.step(p[i])["status"] == 0
+            if not any(left) and not own:
+                break
+        assert not any(left) and not own
+        torch.cuda.synchronize()
+        for g in groups:
+            for i, (_, x) in enumerate(g):
+                assert torch.equal(x.grid(maze.GRID_PHI), want[i][k]), (KINDS[i], k)
+    for g in groups:
+        kept_resident(maze, *(x for _, x in g))
+        for _, x in g:
+            x.close()
+    for b in batches:
+        b.close()
+
+
+@pytest.mark.parametrize("kind", [(32, 0, 1e-9), (100, 0, 1e-6)])
+def test_a_step_is_not_held_by_another_streams_queue(maze, kind):
+    """A thread whose stream still has a second of the caller's work before its
+    step: steps on other streams meanwhile take as long as ever."""
+    import threading
+    import time
+    a = torch.cuda.Stream()
+    with torch.cuda.stream(a):  # cycles of half a second, from a short sleep
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        torch.cuda._sleep(1000)
+        e0.record()
+        torch.cuda._sleep(10000000)
+        e1.record()
+    a.synchronize()
+    half = int(10000000 * 500.0 / e0.elapsed_time(e1))
+    one = torch.ones(1, device="cuda")
+    b = None
+    for _ in range(8):  # a stream that does not share a's hardware queue
+        c = torch.cuda.Stream()
+        with torch.cuda.stream(a):
+            torch.cuda._sleep(half // 5)
+        t0 = time.perf_counter()
+        with torch.cuda.stream(c):
+            one.add_(1)
+        c.synchronize()
+        if time.perf_counter() - t0 < 0.05:
+            b = c
+        a.synchronize()
+        if b is not None:
+            break
+    if b is None:
+        pytest.skip("no stream beside the first one")
+    print(f"case: step beside another stream's queue {kind}", flush=True)
+    sa, xa = on_stream(maze, kind, 70, a)
+    sb, xb = on_stream(maze, kind, 71, b)
+    pa, pb = dev(sa.pos + sa.vel), dev(sb.pos + sb.vel)
+    torch.cuda.synchronize()
+    for x, p in ((xa, pa), (xb, pb), (xa, pa), (xb, pb)):
+        x.step(p)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(a):
+        torch.cuda._sleep(2 * half)
+    t = threading.Thread(target=lambda: xa.step(pa))
+    t.start()
+    time.sleep(0.1)
+    t0 = time.perf_counter()
+    for _ in range(3):
+        xb.step(pb)
+    took = time.perf_counter() - t0
+    waiting = t.is_alive()
+    t.join()
+    torch.cuda.synchronize()
+    assert waiting and took < 0.4, (waiting, took)
+    kept_resident(maze, xa, xb)
+    xa.close()
+    xb.close()
