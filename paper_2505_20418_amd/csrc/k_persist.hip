@@ -654,9 +654,13 @@ size_t persist_bytes(const PersistGeom& g, bool fp32) {
   return kPersistSlotBytes + (size_t)g.nwg * 3 * 2 * (g.mx + g.my) * g.N * (fp32 ? 4 : 8);
 }
 
-// Empties slots and inboxes (once; solves keep them in order).
-__global__ __launch_bounds__(kThreads) void k_persist_empty(uint32_t* q, size_t n, int fp32) {
+// Empties slots and inboxes before the first solve, and before one that
+// follows launched solves or one that gave up; solves that run to their end
+// keep them in order.
+__global__ __launch_bounds__(kThreads) void k_persist_empty(uint32_t* q, size_t n, int fp32,
+                                                            Scalars* sc) {
   const size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x;
+  if (i == 0) ctl_st(&sc->res_iter, 0);
   if (i < n)
     q[i] = (fp32 && i >= kPersistSlotBytes / sizeof(uint32_t))
                ? kPersistEmpty32
@@ -666,7 +670,7 @@ hipError_t launch_persist_empty(const DeviceState& d, const PersistGeom& g, bool
                                 hipStream_t st) {
   const size_t n = persist_bytes(g, fp32) / sizeof(uint32_t);
   hipLaunchKernelGGL(k_persist_empty, dim3((unsigned)((n + kThreads - 1) / kThreads)),
-                     dim3(kThreads), 0, st, reinterpret_cast<uint32_t*>(d.res), n, fp32 ? 1 : 0);
+                     dim3(kThreads), 0, st, reinterpret_cast<uint32_t*>(d.res), n, fp32 ? 1 : 0, d.sc);
   return hipGetLastError();
 }
 

@@ -59,6 +59,9 @@ struct maze_session {
   PersistGeom pgeom{};   // resident solves; nwg = 0: solved by launched sweeps
   int president = 0;     // workgroups of a batched resident launch that fit the device
   int pneed = 0, pcap = 0;  // of a resident solve at the gate
+  // whether the exchange scratch is as a resident solve leaves it; launched
+  // solves keep vectors there
+  bool res_ready = false;
   long long resident_solves = 0, resident_lost = 0;  // run to their end, given up
   hipStream_t stream = nullptr;
   // captured chunks of kPollBatch sweeps, [fp32][parity of the first sweep]
@@ -222,8 +225,11 @@ static PersistGeom persist_geom_of(const maze_config* c, int N) {
   return (c->flags & MAZE_FLAG_MULTIGRID) ? PersistGeom{} : persist_geom(c, N);
 }
 
+static constexpr size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
+
 struct Layout {
   size_t off[64];
+  size_t res = 0;  // of the resident solves' exchange
   size_t total = 0;
   int n = 0;
   size_t add(size_t bytes) {
@@ -262,6 +268,12 @@ static Layout layout_for(const maze_config* c, int N, int* ntx_out, int* ntiles_
   L.add(mixed ? 0 : 2 * gd); // 7 p (two buffers)
   L.add(mixed ? 2 * gf : 0); // 8 r32 (two buffers)
   L.add(mixed ? 2 * gf : 0); // 9 p32 (two buffers)
+  // The exchange of resident solves: in the second r and both p, which only
+  // launched solves use, and what it needs beyond those (some grids below 45^3)
+  if (const size_t res = persist_bytes(persist_geom_of(c, N), mixed)) {
+    L.res = align256(L.off[mixed ? 8 : 6] + (mixed ? gf : gd));
+    L.total = std::max(L.total, align256(L.res + res));
+  }
   L.add(mixed ? gf : 0);     // 10 e32
   L.add(sizeof(double) * (size_t)SL_COUNT * stride);  // partial-sum table
   L.add(sizeof(Scalars));    // 12 scalars
@@ -278,15 +290,12 @@ static Layout layout_for(const maze_config* c, int N, int* ntx_out, int* ntiles_
   L.add(sizeof(double) * (n + 1));        // 23 md_epart
   L.add(sizeof(double) * kHistCap);       // 24 residual history
   L.add(sizeof(int32_t) * (size_t)ntx * (1 + kMaxCandAxis));  // 25 spreading candidates
-  // 26 resident solves; with multigrid too, which does not use it, so that the
-  // flag only ever adds to what maze_device_bytes reports
-  L.add(persist_bytes(persist_geom(c, N), c->precision == MAZE_MIXED));
   if (mg) {
     int Ns[kMgMaxLevels];
     const int levels = mg_plan(N, Ns, kMgMaxLevels);
     const size_t es = (c->precision == MAZE_MIXED) ? sizeof(float) : sizeof(double);
     const bool f32 = es == sizeof(float);
-    L.add(f32 ? es * (size_t)G : 0);  // 27 z (FP64 uses the second r buffer)
+    L.add(f32 ? es * (size_t)G : 0);  // 26 z (FP64 uses the second r buffer)
     for (int l = 1; l < levels; ++l) {
       const size_t gl = (size_t)Ns[l] * Ns[l] * Ns[l];
       L.add(es * gl);  // x_l
@@ -421,6 +430,7 @@ static int chunk_graph(maze_session* s, bool fp32, int par0, void* x, hipGraphEx
 
 static int run_cg(CgJob& job, bool fp32, bool zero_x, int first_batch) {
   maze_session* s = job.s;
+  s->res_ready = false;
   DeviceState& d = s->d;
   const SweepGeom& w = s->sweep;
   const long long guard = sweep_guard(job.max_iter, first_batch);
@@ -512,8 +522,6 @@ struct BatchTable {
   size_t o_geom2 = 0, o_wgb2 = 0;
 };
 static BatchTable g_tables[64];
-
-static constexpr size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 // Offsets of a batch table for cap sessions (and its total size).
 static constexpr BatchTable table_layout(int cap) {
@@ -957,6 +965,16 @@ static bool persist_pays(const std::vector<const maze_session*>& ss) {
   return res <= bytes / 5.0e6 + 12.0 * nmax * (1 + (f32 ? 1 : 0) + (f64 ? 1 : 0));
 }
 
+// Empties the exchange scratch of a session whose last solve was not a resident
+// one that ran to its end.
+static hipError_t persist_ready(maze_session* s) {
+  if (s->res_ready) return hipSuccess;
+  const hipError_t e =
+      launch_persist_empty(s->d, s->pgeom, s->cfg.precision == MAZE_MIXED, s->stream);
+  s->res_ready = e == hipSuccess;
+  return e;
+}
+
 // Queues the resident solves `idx` of jobs (sessions and solution vectors
 // through `job`) on st: one session directly; several of the smaller
 // classes from the table (args,
@@ -967,6 +985,7 @@ static int queue_persist(const std::vector<int>& idx, F job, bool fp32, bool zer
                          hipStream_t st) {
   const unsigned spin = persist_spin();
   std::vector<int> order;
+  for (int i : idx) HIP_TRY(persist_ready(job(i).s));
   for (int i : idx)
     if (idx.size() > 1 && persist_batched(job(i).s->pgeom)) order.push_back(i);
   for (int i : idx) {
@@ -1152,6 +1171,7 @@ static int run_cg_batch(std::vector<CgJob>& jobs, bool fp32, bool zero_x, int fi
   for (int q = 0; q < n; ++q) {
     const int i = order[q];
     maze_session* s = jobs[i].s;
+    s->res_ready = false;
     const SweepGeom& g = shape(i);
     if (g.nwg > s->d.part_stride) return MAZE_E_INVALID;
     if (classes.empty() || cls(order[classes.back().c0]) != cls(i)) {
@@ -1248,6 +1268,7 @@ static int run_sstep_batch(std::vector<CgJob>& jobs, bool fp32, bool zero_x, int
   for (int q = 0; q < n; ++q) {
     const int i = order[q];
     maze_session* s = jobs[i].s;
+    s->res_ready = false;
     const SweepGeom& b = gb(i);
     const SweepGeom& u = gu(i);
     if (b.nwg > s->d.part_stride || u.nwg > s->d.part_stride) return MAZE_E_INVALID;
@@ -1392,6 +1413,7 @@ static int solve_error(int err) { return err == kErrAborted ? kRepeat : MAZE_E_N
 // launched sweeps from here on, the error flag cleared.
 static int persist_off(maze_session* s) {
   s->resident_lost += 1;
+  s->res_ready = false;
   s->pgeom.nwg = 0;
   HIP_TRY(hipStreamSynchronize(s->stream));
   HIP_TRY(hipMemsetAsync(&s->d.sc->err, 0, sizeof(int32_t), s->stream));
@@ -1811,6 +1833,7 @@ static int step_one(maze_session* s, const double* pos, double* field, double* f
   }
   PersistTurn turn;
   HIP_TRY(persist_enter(turn, s->device, s->stream, one, true));
+  HIP_TRY(persist_ready(s));
   HIP_TRY(launch_persist(d, s->pgeom, mixed ? (void*)d.e32 : (void*)d.y, mixed, mixed,
                          s->geom.nwg, persist_spin(), s->stream));
   turn.queued();
@@ -2374,6 +2397,7 @@ int batch_first_unit(maze_batch* b, BatchJob& j, bool zero_x) {
       if (o.phase == kBatchCg && o.s != s && persist_of(o.s)) ss.push_back(o.s);
     res = !batch_mode_forced() && persist_pays(ss);
   }
+  if (!res) s->res_ready = false;
   if (res) {
     j.tp = false;
     // queued by the next maze_batch_advance together with the others
@@ -2872,7 +2896,7 @@ int maze_init(const maze_config* cfg, const double* charges_dev, const double* p
   d.hist_cap = kHistCap;
   d.cand = (int32_t*)at(25);
   s->pgeom = persist_geom_of(cfg, d.N);
-  d.res = s->pgeom.nwg > 0 ? (char*)at(26) : nullptr;
+  d.res = s->pgeom.nwg > 0 ? base + L.res : nullptr;
   d.weight_gradient_force = (cfg->flags & MAZE_FLAG_WEIGHT_GRADIENT_FORCE) ? 1 : 0;
   if (mg) {
     MgHierarchy& m = d.mg;
@@ -2884,10 +2908,10 @@ int maze_init(const maze_config* cfg, const double* charges_dev, const double* p
       m.G[l] = (long long)Ns[l] * Ns[l] * Ns[l];
       m.c[l] = std::pow(0.25, l);
     }
-    m.z = m.fp32 ? at(27) : (void*)(d.r + d.G);
+    m.z = m.fp32 ? at(26) : (void*)(d.r + d.G);
     for (int l = 1; l < m.levels; ++l) {
-      m.x[l] = at(28 + 2 * (l - 1));
-      m.b[l] = at(29 + 2 * (l - 1));
+      m.x[l] = at(27 + 2 * (l - 1));
+      m.b[l] = at(28 + 2 * (l - 1));
     }
   }
   if (hipHostMalloc((void**)&s->host_sc, 2 * sizeof(Scalars), hipHostMallocDefault) !=
@@ -2947,8 +2971,7 @@ int maze_init(const maze_config* cfg, const double* charges_dev, const double* p
   if (hipMemsetAsync(base, 0, L.total, stream) != hipSuccess ||
       hipMemcpyAsync(d.Q, charges_dev, sizeof(double) * n, hipMemcpyDeviceToDevice, stream) !=
           hipSuccess ||
-      launch_cand_table(d, stream) != hipSuccess ||
-      (s->pgeom.nwg > 0 && launch_persist_empty(d, s->pgeom, mixed, stream) != hipSuccess)) {
+      launch_cand_table(d, stream) != hipSuccess) {
     maze_destroy(s);
     return MAZE_E_DEVICE;
   }

@@ -208,7 +208,8 @@ struct DeviceState {
   // residual history of the current CG solve (written by the sweeps)
   double* hist = nullptr;
   int hist_cap = 0;
-  // resident solves: exchange slots, then the workgroups' inboxes
+  // resident solves: exchange slots, then the workgroups' inboxes, in the memory
+  // of vectors that only launched solves use
   char* res = nullptr;
   // multigrid preconditioner (levels == 0: Jacobi)
   MgHierarchy mg;
@@ -352,7 +353,7 @@ int sstep_threads(const SweepGeom& g);
 PersistGeom make_persist_geom(int N, bool fp32);
 size_t persist_bytes(const PersistGeom& g, bool fp32);  // of DeviceState::res
 hipError_t launch_persist_empty(const DeviceState& d, const PersistGeom& g, bool fp32,
-                                hipStream_t st);  // once, before the first solve
+                                hipStream_t st);
 template <typename T>  // a session's entry of the batched launch
 SweepArgs<T> persist_args(const DeviceState& d, T* x, int nprev_first, bool zero_x);
 size_t persist_lds_bytes(const PersistGeom& g, bool fp32);

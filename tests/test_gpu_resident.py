@@ -386,3 +386,49 @@ def test_a_step_is_not_held_by_another_streams_queue(maze, kind):
     kept_resident(maze, xa, xb)
     xa.close()
     xb.close()
+
+
+# exchange partly in memory of its own (20, 32, 44) and all in that of launched
+# solves' vectors
+@pytest.mark.parametrize("N,prec,tol", [(20, 0, 1e-10), (32, 1, 1e-7), (40, 0, 1e-9),
+                                        (44, 0, 1e-9),
+                                        (64, 1, 1e-7), (96, 0, 1e-9), (128, 1, 1e-6)])
+@pytest.mark.parametrize("sstep", [False, True])
+def test_forms_follow_each_other(maze, monkeypatch, N, prec, tol, sstep):
+    """Launched solves (timed steps, batches above the fill level, direct solves
+    among them) leave their vectors where the next resident solve keeps its
+    exchange: the forms may follow each other in any order."""
+    print(f"case: resident and launched solves in turn, N {N} precision {prec}", flush=True)
+    flags = maze.MAZE_FLAG_SSTEP if sstep else 0
+    s, a = make(maze, N, prec, tol, 40 + N, flags=flags)
+    _, other = make(maze, N, prec, tol, 41 + N, flags=flags)
+    monkeypatch.setenv("MAZE_PERSIST", "0")
+    _, b = make(maze, N, prec, tol, 40 + N, flags=flags)
+    monkeypatch.delenv("MAZE_PERSIST")
+    bound = field_bound(s, a, N, tol, maze)
+    plan = ["resident", "timed", "resident", "resident", "batch", "resident", "solve", "timed",
+            "solve", "resident"]
+    for k, form in enumerate(plan):
+        p = dev(s.pos + (k + 1) * s.vel)
+        before = maze.maze_resident_solves(a.handle)["solves"]
+        if form == "timed":
+            maze.maze_profile_enable(a.handle, True)
+        if form == "solve":
+            fa, fb = a.solve(p)["field"], b.solve(p)["field"]
+            assert torch.linalg.norm(fa - fb).item() <= bound, (k, form)
+        elif form == "batch":
+            monkeypatch.setenv("MAZE_BATCH_MODE", "throughput")
+            assert maze.maze_step_batch([a.handle, other.handle], [p, p])[0] == 0
+            monkeypatch.delenv("MAZE_BATCH_MODE")
+        else:
+            assert a.step(p)["status"] == 0
+        if form != "solve":
+            assert b.step(p)["status"] == 0
+        maze.maze_profile_enable(a.handle, False)
+        ran = maze.maze_resident_solves(a.handle)["solves"] - before
+        assert (ran > 0) == (form in ("resident", "solve")), (k, form, ran)
+        d = torch.linalg.norm(a.grid(maze.GRID_PHI) - b.grid(maze.GRID_PHI)).item()
+        assert d <= (k + 1) * bound, (k, form, d)
+    kept_resident(maze, a)
+    for x in (a, b, other):
+        x.close()
