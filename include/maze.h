@@ -162,18 +162,30 @@ size_t maze_device_bytes(const maze_config* cfg);
 int maze_init(const maze_config* cfg, const double* charges_dev,
               const double* pos0_dev, maze_session** out, maze_stats* st);
 
-/* Resident solves (maze_resident_solves counts them). On grids up to 128^3 the Jacobi PLCG (with or without
- * MAZE_FLAG_SSTEP) runs all iterations of a solve in one launch whose
- * workgroups keep x, r, p and A p on the chip and exchange boundary rows and
- * sums (same per-point arithmetic as the launched sweeps; the sums' order,
- * so the last bits, differ). maze_step, maze_solve, maze_step_batch and maze_batch_* all use it,
- * so a session's results stay bitwise those it gets alone; a batch above the
- * fill level (maze_step_batch) runs by launched sweeps where that is faster.
- * Sessions with a forced launch shape, timed ones (maze_profile_enable)
- * and those created with MAZE_PERSIST=0 in the environment use launched
- * sweeps. Waits are bounded: a solve that other work keeps from running as
- * a whole for seconds is repeated by launched sweeps, as are the session's
- * later ones. */
+/* Resident solves (maze_resident_solves counts them). On grids up to 128^3
+ * the Jacobi PLCG, with or without MAZE_FLAG_SSTEP, runs all iterations of a
+ * solve in one launch whose workgroups keep x, r, p and A p on the chip and
+ * exchange boundary rows and sums (same per-point arithmetic as the launched
+ * sweeps; the sums' order, so the last bits, differ). maze_step, maze_solve,
+ * maze_step_batch and maze_batch_* all use it, and a session's results are
+ * bitwise those it gets alone, but for those of a batch at or above the fill
+ * level (see maze_step_batch), which takes the faster of the two forms.
+ * Launched are the solves of sessions with a forced launch shape, of timed
+ * ones (maze_profile_enable), of those created with MAZE_PERSIST=0 in the
+ * environment and of those whose stream is restricted to some of the device's
+ * compute units.
+ *
+ * The workgroups of a resident solve wait for each other. Solves of different
+ * streams and threads run together where the device holds all their
+ * workgroups (several of 64^3 and below); others are queued behind each
+ * other on the device, and a call that finds one queued already waits on the
+ * host. Waits inside a solve are bounded: one that something else on the
+ * device (another process) keeps from running as a whole for about 0.2 s is
+ * repeated by launched sweeps, and the session solves by those for its next
+ * 64 solves, 128 after a second time and so on up to 4096. Then, and in every
+ * other case where both forms are used in turn, results agree to the
+ * tolerance, not bitwise. MAZE_PERSIST_SPIN in the environment sets the
+ * bound (polls of under 1 us). */
 
 /* One MaZe step k -> k+1 (Section 2, equations "SHAKE", "SHAKEy" and
  * "SHAKEPhiFinal"; Appendix B for the Jacobi PLCG):

@@ -63,6 +63,9 @@ struct maze_session {
   // solves keep vectors there
   bool res_ready = false;
   long long resident_solves = 0, resident_lost = 0;  // run to their end, given up
+  // after a solve that gave up: the solves still to be launched ones, and how
+  // many the next one costs
+  int launched_left = 0, launched_span = 64;
   hipStream_t stream = nullptr;
   // captured chunks of kPollBatch sweeps, [fp32][parity of the first sweep]
   // [slot]: a graph holds its kernels' arguments, and the solution vector
@@ -198,6 +201,19 @@ static int device_cus() {
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return 0;
   return cus;
+}
+
+// Whether a stream is restricted to some of the device's CUs (a solve's
+// workgroups might then not all be resident).
+static bool stream_masked(hipStream_t st, int cus) {
+  uint32_t mask[32] = {0};
+  if (hipExtStreamGetCUMask(st, 32, mask) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  int n = 0;
+  for (uint32_t w : mask) n += __builtin_popcount(w);
+  return n > 0 && n < cus;
 }
 
 static int part_stride_for(const DeviceState& d, const MarchGeom& g, const SweepGeom& w) {
@@ -428,9 +444,15 @@ static int chunk_graph(maze_session* s, bool fp32, int par0, void* x, hipGraphEx
   return MAZE_OK;
 }
 
+// Notes that a session's solve is a launched one.
+static void solve_launched(maze_session* s) {
+  s->res_ready = false;
+  if (s->launched_left > 0) --s->launched_left;
+}
+
 static int run_cg(CgJob& job, bool fp32, bool zero_x, int first_batch) {
   maze_session* s = job.s;
-  s->res_ready = false;
+  solve_launched(s);
   DeviceState& d = s->d;
   const SweepGeom& w = s->sweep;
   const long long guard = sweep_guard(job.max_iter, first_batch);
@@ -933,13 +955,14 @@ static int gate_drain(maze_session* s) {
 // by launched sweeps).
 static unsigned persist_spin() {
   const char* e = std::getenv("MAZE_PERSIST_SPIN");
-  return e ? (unsigned)std::strtoul(e, nullptr, 10) : 1u << 21;
+  return e ? (unsigned)std::strtoul(e, nullptr, 10) : 1u << 18;
 }
 
 // Whether a session's next solve runs in the resident form (timed sweeps are
 // launched ones; g_gate has a place for each of the first 64 devices).
 static bool persist_of(const maze_session* s) {
-  return s->pgeom.nwg > 0 && !s->prof && s->device >= 0 && s->device < 64;
+  return s->pgeom.nwg > 0 && s->launched_left == 0 && !s->prof && s->device >= 0 &&
+         s->device < 64;
 }
 
 // Whether the resident solves of `ss` together take less time than one
@@ -1112,9 +1135,11 @@ static int run_cg_batch(std::vector<CgJob>& jobs, bool fp32, bool zero_x, int fi
   if (!launched) {
     std::vector<CgJob> res, rest;
     std::vector<const maze_session*> rs;
+    std::vector<bool> resident;
     for (const CgJob& j : jobs) {
-      (persist_of(j.s) ? res : rest).push_back(j);
-      if (persist_of(j.s)) rs.push_back(j.s);
+      resident.push_back(persist_of(j.s));
+      (resident.back() ? res : rest).push_back(j);
+      if (resident.back()) rs.push_back(j.s);
     }
     // in the throughput shapes (results summed in another order than alone)
     // only where that is the faster form
@@ -1125,7 +1150,7 @@ static int run_cg_batch(std::vector<CgJob>& jobs, bool fp32, bool zero_x, int fi
       if (rc == MAZE_OK && !rest.empty()) rc = run_cg_batch(rest, fp32, zero_x, first_batch);
       if (rc != MAZE_OK) return rc;
       size_t a = 0, b = 0;  // results back into the caller's order
-      for (CgJob& j : jobs) j = persist_of(j.s) ? res[a++] : rest[b++];
+      for (int i = 0; i < n; ++i) jobs[i] = resident[i] ? res[a++] : rest[b++];
       return MAZE_OK;
     }
   }
@@ -1171,7 +1196,7 @@ static int run_cg_batch(std::vector<CgJob>& jobs, bool fp32, bool zero_x, int fi
   for (int q = 0; q < n; ++q) {
     const int i = order[q];
     maze_session* s = jobs[i].s;
-    s->res_ready = false;
+    solve_launched(s);
     const SweepGeom& g = shape(i);
     if (g.nwg > s->d.part_stride) return MAZE_E_INVALID;
     if (classes.empty() || cls(order[classes.back().c0]) != cls(i)) {
@@ -1268,7 +1293,7 @@ static int run_sstep_batch(std::vector<CgJob>& jobs, bool fp32, bool zero_x, int
   for (int q = 0; q < n; ++q) {
     const int i = order[q];
     maze_session* s = jobs[i].s;
-    s->res_ready = false;
+    solve_launched(s);
     const SweepGeom& b = gb(i);
     const SweepGeom& u = gu(i);
     if (b.nwg > s->d.part_stride || u.nwg > s->d.part_stride) return MAZE_E_INVALID;
@@ -1409,12 +1434,16 @@ static int recover_error(maze_session* s) {
 constexpr int kRepeat = 1 << 20;
 static int solve_error(int err) { return err == kErrAborted ? kRepeat : MAZE_E_NONFINITE; }
 
-// Makes a session whose resident solve gave up ready for its repetition:
-// launched sweeps from here on, the error flag cleared.
-static int persist_off(maze_session* s) {
+// Makes a session whose resident solve gave up ready for its repetition: the
+// error flag cleared, and launched sweeps for its next solves, twice as many
+// after each solve given up, so that a device that is shared for good costs
+// one bounded wait (about 0.2 s) in 4096 solves, and one that was busy for
+// a while is used again.
+static int persist_rest(maze_session* s) {
   s->resident_lost += 1;
   s->res_ready = false;
-  s->pgeom.nwg = 0;
+  s->launched_left = s->launched_span;
+  s->launched_span = std::min(2 * s->launched_span, 4096);
   HIP_TRY(hipStreamSynchronize(s->stream));
   HIP_TRY(hipMemsetAsync(&s->d.sc->err, 0, sizeof(int32_t), s->stream));
   return MAZE_OK;
@@ -1700,7 +1729,7 @@ static int direct_solve(maze_session* s, int guess, const double* pos, double* x
     rc = solve_multi(one, xs, rcs);
     if (rc != MAZE_OK) return rc;
     if (rcs[0] != kRepeat) break;
-    rc = persist_off(s);
+    rc = persist_rest(s);
     if (rc != MAZE_OK) return rc;
   }
   if (rcs[0] == MAZE_E_NONFINITE) return recover_error(s);
@@ -1742,7 +1771,7 @@ static int step_multi(std::vector<maze_session*>& ss, const double* const* pos,
   std::vector<int> again_rcs;
   for (int i = 0; i < n; ++i) {
     if (rcs[i] != kRepeat) continue;
-    rc = persist_off(ss[i]);
+    rc = persist_rest(ss[i]);
     if (rc == MAZE_OK) rc = step_rhs(ss[i]);
     if (rc != MAZE_OK) return rc;
     again.push_back(ss[i]);
@@ -1873,7 +1902,7 @@ static int step_one(maze_session* s, const double* pos, double* field, double* f
     std::vector<double*> ys{d.y};
     std::vector<int> rcs;
     if (err == kErrAborted) {
-      rc = persist_off(s);
+      rc = persist_rest(s);
       if (rc == MAZE_OK) rc = step_rhs(s);
       if (rc == MAZE_OK) rc = solve_multi(one, ys, rcs);
     } else {
@@ -1881,7 +1910,7 @@ static int step_one(maze_session* s, const double* pos, double* field, double* f
       HIP_TRY(hipMemsetAsync(&d.sc->err, 0, sizeof(int32_t), s->stream));
       rc = solve_multi(one, ys, rcs, &v);
       if (rc == MAZE_OK && rcs[0] == kRepeat) {
-        rc = persist_off(s);
+        rc = persist_rest(s);
         if (rc == MAZE_OK) rc = step_rhs(s);
         if (rc == MAZE_OK) rc = solve_multi(one, ys, rcs);
       }
@@ -2397,7 +2426,7 @@ int batch_first_unit(maze_batch* b, BatchJob& j, bool zero_x) {
       if (o.phase == kBatchCg && o.s != s && persist_of(o.s)) ss.push_back(o.s);
     res = !batch_mode_forced() && persist_pays(ss);
   }
-  if (!res) s->res_ready = false;
+  if (!res) solve_launched(s);
   if (res) {
     j.tp = false;
     // queued by the next maze_batch_advance together with the others
@@ -2664,7 +2693,7 @@ int batch_process(maze_batch* b, const maze_batch::Poll& P) {
     }
     if (h.err == kErrAborted) {
       // a resident solve gave up waiting: the step's solve again, launched
-      int rc = persist_off(s);
+      int rc = persist_rest(s);
       if (rc == MAZE_OK) rc = step_rhs(s);
       if (rc != MAZE_OK) return rc;
       if (j.fp32) {
@@ -2935,6 +2964,7 @@ int maze_init(const maze_config* cfg, const double* charges_dev, const double* p
   if (forced_shape(d, mixed, &forced) ||
       (sstep_of(s) && (forced_basis(d, mixed, &forced) || forced_update(d, mixed, &forced))))
     s->pgeom.nwg = 0;
+  if (s->pgeom.nwg > 0 && stream_masked(stream, device_cus())) s->pgeom.nwg = 0;
   if (s->pgeom.nwg > 0) {
     const int cus = device_cus();
     const bool batched = persist_batched(s->pgeom);

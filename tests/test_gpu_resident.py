@@ -432,3 +432,79 @@ def test_forms_follow_each_other(maze, monkeypatch, N, prec, tol, sstep):
     kept_resident(maze, a)
     for x in (a, b, other):
         x.close()
+
+
+def test_resident_again_after_a_solve_that_gave_up(maze, monkeypatch):
+    """A solve that gave up costs the session its next 64 resident solves, the
+    second one 128; in between they are resident again, from a clean exchange."""
+    N, tol = 20, 1e-9
+    print("case: resident again after a solve given up", flush=True)
+    s, x = make(maze, N, 0, tol, 15)
+    _, y = make(maze, N, 0, tol, 16)
+    monkeypatch.setenv("MAZE_PERSIST", "0")
+    _, ref = make(maze, N, 0, tol, 15)
+    monkeypatch.delenv("MAZE_PERSIST")
+    p = [dev(s.pos + s.vel * math.sin(0.3 * (k + 1))) for k in range(7)]
+    bound = field_bound(s, x, N, tol, maze)
+    k, rests = 0, (64, 128)
+    for lost, rest in enumerate(rests, 1):
+        monkeypatch.setenv("MAZE_PERSIST_SPIN", "0")
+        assert x.step(p[k % 7])["status"] == 0
+        monkeypatch.delenv("MAZE_PERSIST_SPIN")
+        ref.step(p[k % 7])
+        k += 1
+        done = maze.maze_resident_solves(x.handle)["solves"]
+        # the step's own repetition is the first of them; a batch's members
+        # that are launched and those that are not keep their places
+        for i in range(rest - 1):
+            got = maze.maze_resident_solves(x.handle)
+            assert got == dict(resident=False, solves=done, given_up=lost), (lost, i)
+            if i == rest - 2:
+                assert maze.maze_step_batch([y.handle, x.handle], [p[k % 7], p[k % 7]])[0] == 0
+            else:
+                assert x.step(p[k % 7])["status"] == 0
+            ref.step(p[k % 7])
+            k += 1
+        assert maze.maze_resident_solves(x.handle)["resident"]
+        for i in range(3):
+            assert x.step(p[k % 7])["status"] == 0
+            ref.step(p[k % 7])
+            k += 1
+        got = maze.maze_resident_solves(x.handle)
+        assert got == dict(resident=True, solves=done + 3, given_up=lost)
+        # each step of either leaves its residual, and a step's error reaches
+        # the next one twice over at most: the last ones bound the rest
+        d = torch.linalg.norm(x.grid(maze.GRID_PHI) - ref.grid(maze.GRID_PHI)).item()
+        assert d <= k * bound, (k, d)
+    kept = maze.maze_resident_solves(y.handle)
+    assert kept["given_up"] == 0
+    for z in (x, y, ref):
+        z.close()
+
+
+def test_stream_with_some_of_the_compute_units(maze):
+    """On a stream restricted to a part of the device, a solve's workgroups might
+    not all be resident: its sessions are launched ones from the start."""
+    import ctypes
+    hip = ctypes.CDLL("libamdhip64.so")
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    words = (cus + 31) // 32
+    mask = (ctypes.c_uint32 * words)(*[0x0000FFFF] * words)
+    st = ctypes.c_void_p()
+    if hip.hipExtStreamCreateWithCUMask(ctypes.byref(st), words, mask) != 0:
+        pytest.skip("no CU mask on this device")
+    print("case: a stream with half of the compute units", flush=True)
+    s, x = make(maze, 64, 0, 1e-9, 17, stream=st.value)
+    _, y = make(maze, 64, 0, 1e-9, 17)
+    p = dev(s.pos + s.vel)
+    torch.cuda.synchronize()
+    assert maze.maze_resident_solves(y.handle)["resident"]
+    got = maze.maze_resident_solves(x.handle)
+    assert got == dict(resident=False, solves=0, given_up=0)
+    assert x.step(p)["status"] == 0 and y.step(p)["status"] == 0
+    torch.cuda.synchronize()
+    d = torch.linalg.norm(x.grid(maze.GRID_PHI) - y.grid(maze.GRID_PHI)).item()
+    assert d <= field_bound(s, y, 64, 1e-9, maze)
+    x.close()
+    y.close()
+    hip.hipStreamDestroy(st)
