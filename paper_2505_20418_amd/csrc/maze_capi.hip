@@ -866,6 +866,9 @@ class PersistTurn {
     const uint64_t lane = st == hipStreamPerThread ? ~(uint64_t)g.led.last
                                                    : (uint64_t)(uintptr_t)st;
     uint32_t behind = 0;
+    // at most 10 ms on the host: batches that keep a solve queued all the time
+    // must not keep a call out
+    const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(10);
     for (;;) {
       for (int i = 0; i < GateLedger::kMax; ++i)
         if (g.led.at[i].id && g.recorded[i]) {
@@ -880,7 +883,7 @@ class PersistTurn {
         g.led.remove(o, g.led.at[o].id);
       }
       behind = g.led.waits(lane, need, cap);
-      if (!host || !behind || !g.led.waiting()) break;
+      if (!host || !behind || !g.led.waiting() || std::chrono::steady_clock::now() >= until) break;
       // a solve of a continuous batch ends without a call to tell
       g.ends.wait_for(lk_, std::chrono::microseconds(200));
     }

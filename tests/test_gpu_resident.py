@@ -508,3 +508,63 @@ def test_stream_with_some_of_the_compute_units(maze):
     x.close()
     y.close()
     hip.hipStreamDestroy(st)
+
+
+def test_steps_get_their_turn_beside_busy_batches(maze):
+    """Two threads that keep continuous batches of large solves going, each
+    queueing its next solve behind the other's: a session on a stream of its own
+    still gets its turn."""
+    import threading
+    import time
+    kind = (96, 0, 1e-8)
+    print(f"case: steps beside busy batches {kind}", flush=True)
+    want = alone_fields(maze, kind, 60, 4)
+    stop, failed = threading.Event(), []
+
+    def busy(seed):
+        try:
+            st = torch.cuda.Stream()
+            made = [on_stream(maze, kind, seed + i, st) for i in range(2)]
+            b = maze.Batch(max_sessions=4, stream=st.cuda_stream)
+            pos = [[dev(s.pos + f * s.vel) for f in (1.0, 2.0)] for s, _ in made]
+            torch.cuda.synchronize()
+            ready.wait()
+            k, flying = [0, 0], [False, False]
+            while not stop.is_set() or any(flying):
+                for i, (_, x) in enumerate(made):
+                    if not flying[i] and not stop.is_set():
+                        b.add(x.handle, pos[i][k[i] % 2], tag=i)
+                        k[i] += 1
+                        flying[i] = True
+                b.advance()
+                for tag, res in b.take():
+                    assert res["status"] == 0
+                    flying[tag] = False
+            kept_resident(maze, *(x for _, x in made))
+            b.close()
+            for _, x in made:
+                x.close()
+        except BaseException as e:  # noqa: BLE001
+            failed.append(e)
+            stop.set()
+    ready = threading.Barrier(3)
+    threads = [threading.Thread(target=busy, args=(20 * t,)) for t in (1, 2)]
+    for t in threads:
+        t.start()
+    s, x = on_stream(maze, kind, 60, torch.cuda.Stream())
+    pos = [dev(s.pos + (k + 1) * s.vel) for k in range(4)]
+    torch.cuda.synchronize()
+    ready.wait()
+    time.sleep(0.05)
+    t0 = time.perf_counter()
+    for k in range(4):
+        assert x.step(pos[k])["status"] == 0
+        assert torch.equal(x.grid(maze.GRID_PHI), want[k]), k
+    took = time.perf_counter() - t0
+    stop.set()
+    for t in threads:
+        t.join()
+    assert not failed, failed
+    assert took < 1.0, took  # four of 1.4 ms alone, each behind some of theirs
+    kept_resident(maze, x)
+    x.close()
