@@ -29,7 +29,8 @@
  *    update, force interpolation) may still be running on the stream. A
  *    non-NULL maze_stats* makes the call synchronise the stream before it
  *    returns.
- *  - A session is not thread safe; different sessions are independent.
+ *  - A session is not thread safe; different sessions are independent
+ *    (their resident solves may queue behind each other, see below).
  *  - Return codes: MAZE_OK; MAZE_NOT_CONVERGED (> 0, a warning: outputs
  *    were written and the state advanced); negative = error, nothing was
  *    written and the state is unchanged.
@@ -77,16 +78,20 @@ enum {
      HIP graph of kPollBatch sweeps (instantiated on first use per
      precision, parity and solution vector, up to 4 per precision and
      parity, freed by maze_destroy) instead of kernel by kernel; same
-     kernels and arguments, so results are bitwise those without it. Needs a non-null cfg.stream (MAZE_E_INVALID otherwise);
-     single-session solves only (batched and multigrid solves launch
-     directly); ignored while maze_profile_enable is on. */
+     kernels and arguments, so results are bitwise those without it. Needs a
+     non-null cfg.stream (MAZE_E_INVALID otherwise). Batched solves replay
+     graphs too where every session of the batch has the flag. No effect on
+     resident solves (see maze_resident_solves), which are one launch
+     already, on multigrid solves, and while maze_profile_enable is on. */
   MAZE_FLAG_GRAPH_CHUNKS = 8,
   /* run the Jacobi PLCG two iterations per pass pair: the s-step CG (s = 2)
      of Chronopoulos and Gear, whose iterates equal those of the PLCG of
      Appendix B in exact arithmetic. A basis kernel forms
      [p, Bp, B^2 p, r/6, B r/6] (B = A/6 - I) and its Gram sums; an
      update kernel applies two iterations' coefficients. 32 bytes per point
-     per two iterations in FP32 (64 in FP64), against 48 (96). The test on
+     per two iterations in FP32 (64 in FP64), against 48 (96). On grids whose
+     solves are resident (up to 128^3, see maze_resident_solves) those take
+     its place, one iteration at a time with the vectors on the chip. The test on
      the residual after the first of the two iterations uses its Gram form;
      with MAZE_NORM_ABSMAX the test runs every two iterations. Not with
      MAZE_FLAG_MULTIGRID (MAZE_E_INVALID). Batches run batched forms of both
@@ -219,11 +224,14 @@ int maze_solve(maze_session* s, int guess, const double* pos_dev,
  * device and the stream of sessions[0]. Per-session semantics and outputs are
  * those of maze_step. Each session has two launch shapes (maze_launch_shape):
  * a batch whose sessions together need fewer than 256 workgroups in their
- * throughput shapes is swept in the latency shapes, and each session's
- * result is then bitwise the one it gets stepped alone; a larger batch is
- * swept in the throughput shapes, and each result then meets the session's
- * tolerance but sums in another order (MAZE_BATCH_MODE=latency or
- * =throughput in the environment forces one mode). pos_dev[i], forces_dev[i] (forces_dev or an entry may be
+ * throughput shapes is swept in the latency shapes (or by resident solves
+ * where the session alone is), and each session's result is then bitwise the
+ * one it gets stepped alone; a larger batch is swept in the throughput
+ * shapes, and each result then meets the session's tolerance but sums in
+ * another order, or its sessions that have resident solves take those where
+ * that is estimated to be faster (MAZE_BATCH_MODE=latency or =throughput in
+ * the environment forces one mode, throughput without resident solves).
+ * pos_dev[i], forces_dev[i] (forces_dev or an entry may be
  * NULL) belong to session i; energies_dev (count doubles, device) and st
  * (count entries, host) may be NULL; st[i].status holds session i's status.
  * A session whose positions are rejected is left unchanged while the others
@@ -282,7 +290,9 @@ int maze_load(maze_session* s, const void* host_buf, size_t bytes);
  * two entries hold the total ms of the update kernels of the timed FP64 and
  * FP32 outer steps. Enabling creates the events (the only allocation
  * outside maze_init). Sampling adds event records to the stream: about 0.5%
- * of a 256^3 step. */
+ * of a 256^3 step. A session of resident solves (maze_resident_solves) is
+ * solved by launched kernels while enabled: 128^3 FP64 MD steps 189 per
+ * second then, 447 without. */
 int maze_profile_enable(maze_session* s, int on);
 int maze_profile_read(maze_session* s, double* out8);
 
@@ -477,8 +487,11 @@ void maze_tcf_destroy(maze_tcf* t);
  * a step that arrives while others are on the device overlaps with them.
  * Per session the kernels, launch shapes and stopping decisions are those of
  * maze_step / maze_md_step alone (each session keeps its own latency
- * shapes), so every result is bitwise the one the session gets stepped
- * alone. Not for multigrid sessions. All sessions of a batch share its
+ * shapes), so a result is bitwise the one the session gets stepped alone,
+ * unless its solve starts while the running ones need 256 workgroups or more in
+ * their throughput shapes, as for maze_step_batch. Resident solves join no
+ * launch: they are queued, those that are ready together, by
+ * maze_batch_advance. Not for multigrid sessions. All sessions of a batch share its
  * device and stream. */
 typedef struct maze_batch maze_batch;
 
@@ -496,7 +509,8 @@ int maze_batch_create(void* stream, int32_t max_sessions, maze_batch** out);
  * step is taken); else a MaZe step at positions pos_dev (device, n*3 doubles) whose
  * forces (forces_dev, n*3) and energy (energy_dev, 1 double) are written
  * when it finishes (either may be NULL). The step's assignment, right-hand
- * side and first CG unit are queued at once. tag is returned with the
+ * side and first CG unit are queued at once (a resident solve by the next
+ * maze_batch_advance). tag is returned with the
  * result. MAZE_E_CAPACITY when the batch is full; MAZE_E_INVALID for a
  * session already in flight, on another device or stream, or multigrid. */
 int maze_batch_add(maze_batch* b, maze_session* s, const maze_md_state* md,

@@ -19,11 +19,12 @@
 // The per-point arithmetic and its order are the fused sweep's (k_cg.hip),
 // so are the iterates up to the rounding of the sums' order.
 //
-// What bounds it: the exchange. Every iteration ends in one all-to-all of
-// the workgroups' sums, a store that has to reach the level shared by the
+// What bounds it: on small grids the exchange. Every iteration ends in one
+// all-to-all of the workgroups' sums, a store that has to reach the level shared by the
 // XCDs and a load that finds it there. The launched form pays a kernel's
 // start and end, the halo planes of its march and six or more dependent
-// plane steps instead.
+// plane steps instead. At 128^3 FP64 (8.4 us an iteration) vector instructions
+// take 63% of the SIMDs' issue, at 64^3 FP32 (3.6 us) about half.
 //
 // Exchange. All data that crosses workgroups moves through stores and loads
 // with agent-scope cache policy, which bypass the caches private to an XCD,
@@ -47,12 +48,13 @@
 // there (Scalars::res_iter).
 //
 // The workgroups of a solve wait for each other, so they have to be resident
-// together: a launch never exceeds what the device holds, and the launches
-// of one process on a device never overlap (PersistGate in maze_capi.hip).
+// together: a launch never exceeds what the device holds, and launches of one
+// process overlap on a device only as far as it holds them all (resident_gate.h).
 // Should they be kept from running together all the same (another process's
 // kernels), every wait is bounded: a workgroup that has polled `spin` times
 // sets err = kErrAborted and leaves, as in turn do all others, and the host
-// repeats the solve with the launched kernels.
+// repeats the solve with the launched kernels; the exchange is emptied before the
+// session's next resident solve.
 #include <algorithm>
 #include <type_traits>
 #include <utility>

@@ -953,7 +953,7 @@ static int gate_drain(maze_session* s) {
   return MAZE_OK;
 }
 
-// Polls after which a workgroup gives up (about 1 us each).
+// Polls after which a workgroup gives up (0.8 us each, 0.2 s in all).
 // MAZE_PERSIST_SPIN in the environment sets it (0: every solve is repeated
 // by launched sweeps).
 static unsigned persist_spin() {
@@ -972,11 +972,14 @@ static bool persist_of(const maze_session* s) {
 // batched solve of them by launched sweeps. Resident solves run (nearly) one
 // after the other, each at the latency of its exchange; a batched sweep moves
 // every session's bytes at the copy rate, with some 12 us per launch and class
-// as its floor. Iteration counts grow as N. Measured, with longer kernels around
-// the solves than now (10.9 and 31.2 ms): 16 sessions of 32^3 to
-// 128^3, half FP64, 13.6 ms against 24.2 ms launched; 64 mixed replicas of
-// 32^3 to 96^3 51.0 ms against 34.9 ms, so the line lies between; the
-// estimates of the two cases are 7.2 against 13.5 and 23 against 14.5.
+// as its floor. Iteration counts grow as N. Only the ratio of the two estimates
+// counts; both are about half the time of a step. Measured, MD steps, resident
+// against launched: 64 sessions of 32^3 FP64 6.4 ms against 10.5, 8 of 64^3 3.0
+// against 5.5, 16 of 96^3 23.5 against 33.4, 16 of 128^3 37 against 84 (mixed 27
+// against 37); launched are 16 of 64^3 (7.4 FP64, 5.3 mixed), 16 of 96^3
+// mixed (16.0) and 64 mixed of 32^3 to 96^3 (31 to 32; resident 51). Over 92
+// batches of 2 to 64 members, both precisions and CG forms, the choice never took
+// over 3% longer than launched solves, the spread between runs of one form.
 static bool persist_pays(const std::vector<const maze_session*>& ss) {
   double res = 0, bytes = 0;
   int nmax = 0;
@@ -2325,7 +2328,9 @@ static void autotune_sstep(maze_session* s) {
 // kernels has completed. Each session keeps its own latency shapes (the
 // basis, update and sweep shapes it uses alone) and the same per-workgroup
 // code, and the sessions' iterations are independent, so a step's result is
-// bitwise the one it gets stepped alone, whatever else is in flight.
+// bitwise the one it gets stepped alone, unless it starts while the running
+// solves fill the device (batch_solve_tp). Resident solves join no launch: those
+// that wait are queued together by the next advance.
 namespace {
 enum BatchPhase { kBatchCg = 0, kBatchCheck = 1, kBatchFinish = 2 };
 
